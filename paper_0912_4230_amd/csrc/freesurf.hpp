@@ -4,16 +4,17 @@
 // cells (Eq. equilempty) and the conversion of cells as they fill and empty
 // (flowchart of Sec. 4: stream the mass, redefine the cell classes).
 //
-// One step is five launches, plus one on moment steps:
+// One step is four launches, plus one on moment steps:
 //   k_fs_step        pull + gas-side reconstruction + mass exchange + collision
 //                    of liquid and interface cells; conversion flags (w1) of
 //                    interface cells
-//   k_fs_mark_fill   filling cells mark their gas neighbours to become interface
-//                    cells and keep emptying neighbours
-//   k_fs_mark_empty  cells that empty mark their liquid neighbours to become
-//                    interface cells; marked gas cells get the equilibrium of
-//                    their neighbours' mean state
-//   k_fs_excess      excess mass of each converted cell, split over its receivers
+//   k_fs_mark        filling cells mark their gas neighbours to become interface
+//                    cells; cells that would empty next to a filling one stay,
+//                    the others mark their liquid neighbours to become interface
+//                    cells
+//   k_fs_convert     marked gas cells get the equilibrium of their neighbours'
+//                    mean state; excess mass of each converted cell, split over
+//                    its receivers
 //   k_fs_final       new classes, masses and fill fractions
 //   k_fs_moments     moments and FP64 diagnostics (moment steps only)
 // Liquid cells cost one byte read and one byte written more than the
@@ -439,7 +440,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>:
 // into one byte carry the same value.
 //   w1: the FILL / EMPTY flag of pass 1 (0 elsewhere)
 //   w2: FS_BORN (gas cell next to a filling cell), FS_KEEP (emptying cell next
-//       to a filling cell: it stays), FS_TO_IF (liquid cell next to a cell that
+//       to a filling cell: it stays, and marks itself), FS_TO_IF (liquid cell next to a cell that
 //       empties), FS_RECV (a receiver of excess mass); zero outside the marked
 //       cells.  The last pass clears the marks of cells that were not interface
 //       cells (it reads FS_KEEP marks of neighbours, so those stay); pass 1 of
@@ -573,9 +574,14 @@ __device__ inline void gather(const T *P, const Nbr &b, int *v)
     if constexpr (Q + 1 < NQ) gather<T, Q + 1>(P, b, v);
 }
 
-// Pass 2.  Every filling cell marks its gas neighbours FS_BORN and its
-// emptying neighbours FS_KEEP.
-__global__ __launch_bounds__(BLOCK) void k_fs_mark_fill(const BatchArgs a)
+// Pass 2.  Every filling cell marks its gas neighbours FS_BORN; every cell
+// that would empty keeps itself (FS_KEEP) when a neighbour fills, else marks
+// its liquid neighbours FS_TO_IF.  Reads no mark.  (A pass of its own for
+// FS_TO_IF, after FS_KEEP marks written by the filling cells, was a launch
+// more: the four
+// class passes of the 256^3 penetration step 24 -> 19 us of 290 without
+// conversions, the 140 x 140 x 1 drop's step 35.3 -> 32.0, 64^3 27 -> 24.)
+__global__ __launch_bounds__(BLOCK) void k_fs_mark(const BatchArgs a)
 {
     const FsTile t = fs_tile(a);
     const GL FsDev *__restrict__ F = t.F;
@@ -593,30 +599,43 @@ __global__ __launch_bounds__(BLOCK) void k_fs_mark_fill(const BatchArgs a)
             const u32x4 f = ld16(F->w1, t.base);
             if (any_byte(f))
                 for (int k = 0; k < FS_CPT; ++k)
-                    if (t.base + k < t.ncell && byte_of(f, k) == FS_FILL) mask |= 1u << k;
+                    if (t.base + k < t.ncell && byte_of(f, k) != 0) mask |= 1u << k;
         }
     }
     if (__builtin_amdgcn_ballot_w64(mask != 0u) == 0) return;   // uniform over the wave
     for_items(mask, t.base, [&](uint32_t idx) {
+        const bool fills = ldg<uint8_t>(F->w1, idx) == FS_FILL;
         const Nbr b = nbr_of(t.L, idx);
         int c[NQ], f[NQ];
         gather(F->cls, b, c);
         gather(F->w1, b, f);
+        bool near_fill = false;
+        for_links([&](auto qc) { near_fill = near_fill || f[decltype(qc)::value] == FS_FILL; });
+        if (!fills && near_fill) {
+            mark(F, idx, FS_KEEP);
+            return;
+        }
+        const int from = fills ? FS_GAS : FS_LIQ;
+        const uint8_t to = fills ? FS_BORN : FS_TO_IF;
         for_links([&](auto qc) {
             constexpr int Q = decltype(qc)::value;
-            const uint32_t j = shifted<Q, 1>(b);
-            if (c[Q] == FS_GAS) mark(F, j, FS_BORN);
-            else if (f[Q] == FS_EMPTY) mark(F, j, FS_KEEP);
+            if (c[Q] == from) mark(F, shifted<Q, 1>(b), to);
         });
     });
 }
 
-// Pass 3.  Every cell that empties marks its liquid neighbours FS_TO_IF;
-// every FS_BORN cell takes the equilibrium of the mean density and velocity
-// of the post-collision populations of its liquid and interface neighbours
-// that do not empty, with m = 0.
+// does a cell with these bytes convert (fill, or empty after all)?
+__device__ inline bool converts(int w1, int w2) { return w1 == FS_FILL || empties(w1, w2); }
+
+// Pass 3.  Every FS_BORN cell takes the equilibrium of the mean density and
+// velocity of its interface neighbours that do not empty (rho and V' of the
+// step), with m = 0.  Excess mass of each converted cell (m - rho when it
+// filled, m when it emptied), split equally over its neighbours that end the
+// step as interface cells without converting; without any, it is lost (and
+// counted).  The marks of pass 2 do not change in this pass; it adds FS_RECV to
+// bytes whose other bits it reads, so either value serves.
 template <class S>
-__global__ __launch_bounds__(BLOCK) void k_fs_mark_empty(const BatchArgs a)
+__global__ __launch_bounds__(BLOCK) void k_fs_convert(const BatchArgs a)
 {
     using R = typename Codec<S>::R;
     [[maybe_unused]] constexpr bool HW = HwMath<S>::value;
@@ -631,28 +650,38 @@ __global__ __launch_bounds__(BLOCK) void k_fs_mark_empty(const BatchArgs a)
         if (any_byte(f) || any_byte(m2))
             for (int k = 0; k < FS_CPT; ++k) {
                 const int w1 = byte_of(f, k), w2 = byte_of(m2, k);
-                if (t.base + k < t.ncell && (empties(w1, w2) || (w2 & FS_BORN))) mask |= 1u << k;
+                if (t.base + k < t.ncell && (converts(w1, w2) || (w2 & FS_BORN))) mask |= 1u << k;
             }
     }
     if (__builtin_amdgcn_ballot_w64(mask != 0u) == 0) return;   // uniform over the wave
     for_items(mask, t.base, [&](uint32_t idx) {
-        // neither byte of a cell that empties or is born is written in this pass
-        const int w1 = ldg<uint8_t>(F->w1, idx), w2 = ldg<uint8_t>(F->w2, idx);
+        const int w1 = ldg<uint8_t>(F->w1, idx);
+        const double m = ldg<double>(F->mass, idx), rho = ldg<double>(F->rho, idx);
         const Nbr b = nbr_of(L, idx);
-        int c[NQ];
+        int c[NQ], f[NQ], m2[NQ];
         gather(F->cls, b, c);
-        if (empties(w1, w2)) {
+        gather(F->w1, b, f);
+        gather(F->w2, b, m2);
+        if (w1 != 0) {   // flagged and not kept: it converts
+            int n = 0;
+            uint32_t recv = 0;
             for_links([&](auto qc) {
                 constexpr int Q = decltype(qc)::value;
-                if (c[Q] == FS_LIQ) mark(F, shifted<Q, 1>(b), FS_TO_IF);
+                const bool r = (c[Q] == FS_IF && !converts(f[Q], m2[Q])) || (m2[Q] & (FS_BORN | FS_TO_IF));
+                recv |= r ? bit(Q) : 0u;
+                n += r ? 1 : 0;
+            });
+            const double ex = w1 == FS_FILL ? m - rho : m;
+            stg<double>(F->share, idx, n ? ex / n : 0.0);
+            if (!n) atomicAdd(F->lost, ex);
+            // mark the receivers: every writer of a mark byte writes the same value
+            for_links([&](auto qc) {
+                constexpr int Q = decltype(qc)::value;
+                if (recv & bit(Q)) mark(F, shifted<Q, 1>(b), (uint8_t)(m2[Q] | FS_RECV));
             });
         } else {
             // born: a gas cell has no liquid neighbour, so the qualifying
             // neighbours are interface cells, whose rho and V' pass 1 stored
-            // (an interface neighbour's mark byte is not written in this pass)
-            int f[NQ], m2[NQ];
-            gather(F->w1, b, f);
-            gather(F->w2, b, m2);
             double rs = 0.0, us[3] = {0.0, 0.0, 0.0};
             int n = 0;
             for_groups([&](auto gc) {
@@ -691,57 +720,7 @@ __global__ __launch_bounds__(BLOCK) void k_fs_mark_empty(const BatchArgs a)
     });
 }
 
-// does a cell with these bytes convert (fill, or empty after all)?
-__device__ inline bool converts(int w1, int w2) { return w1 == FS_FILL || empties(w1, w2); }
-
-// Pass 4.  Excess mass of each converted cell (m - rho when it filled, m when
-// it emptied), split equally over its neighbours that end the step as
-// interface cells without converting; without any, it is lost (and counted).
-__global__ __launch_bounds__(BLOCK) void k_fs_excess(const BatchArgs a)
-{
-    const FsTile t = fs_tile(a);
-    const GL FsDev *__restrict__ F = t.F;
-    uint32_t mask = 0;
-    if (row_work(t)) {
-        const u32x4 f = ld16(F->w1, t.base);
-        if (any_byte(f)) {
-            const u32x4 m2 = ld16(F->w2, t.base);
-            for (int k = 0; k < FS_CPT; ++k) {
-                const int w1 = byte_of(f, k);
-                if (t.base + k < t.ncell && converts(w1, byte_of(m2, k))) mask |= 1u << k;
-            }
-        }
-    }
-    if (__builtin_amdgcn_ballot_w64(mask != 0u) == 0) return;   // uniform over the wave
-    for_items(mask, t.base, [&](uint32_t idx) {
-        const int w1 = ldg<uint8_t>(F->w1, idx);
-        const double m = ldg<double>(F->mass, idx), rho = ldg<double>(F->rho, idx);
-        const Nbr b = nbr_of(t.L, idx);
-        int c[NQ], f[NQ], m2[NQ];
-        gather(F->cls, b, c);
-        gather(F->w1, b, f);
-        gather(F->w2, b, m2);
-        int n = 0;
-        uint32_t recv = 0;
-        for_links([&](auto qc) {
-            constexpr int Q = decltype(qc)::value;
-            const bool r = (c[Q] == FS_IF && !converts(f[Q], m2[Q])) || (m2[Q] & (FS_BORN | FS_TO_IF));
-            recv |= r ? bit(Q) : 0u;
-            n += r ? 1 : 0;
-        });
-        const double ex = w1 == FS_FILL ? m - rho : m;
-        stg<double>(F->share, idx, n ? ex / n : 0.0);
-        if (!n) atomicAdd(F->lost, ex);
-        // mark the receivers: every writer of a mark byte writes the same value
-        // (the other bits do not change in this pass)
-        for_links([&](auto qc) {
-            constexpr int Q = decltype(qc)::value;
-            if (recv & bit(Q)) mark(F, shifted<Q, 1>(b), (uint8_t)(m2[Q] | FS_RECV));
-        });
-    });
-}
-
-// Pass 5.  New classes of the converted and marked cells; the final mass and
+// Pass 4.  New classes of the converted and marked cells; the final mass and
 // fill fraction of the interface cells that changed: their own mass (rho for
 // a liquid cell that became one, 0 for a gas cell that did) plus the shares
 // of their converting neighbours (FS_RECV cells only); marks of cells that
@@ -854,7 +833,7 @@ __global__ __launch_bounds__(BLOCK) void k_fs_final(const BatchArgs a)
     }
 }
 
-// Moment steps, after pass 5 (one thread per cell, the step grid): rho, V'
+// Moment steps, after pass 4 (one thread per cell, the step grid): rho, V'
 // and lambda of the step into the moments buffer (gas and solid cells 0) and
 // the FP64 diagnostic partials over liquid and interface cells, with
 // diag[4] = the liquid mass (m of interface cells, rho of liquid cells).

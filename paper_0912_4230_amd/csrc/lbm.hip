@@ -325,9 +325,8 @@ template <class S, bool FT, bool ST>
 void launch_fs(const FsGrids &g, hipStream_t s)
 {
     hipLaunchKernelGGL((k_fs_step<S, FT, ST>), dim3(g.blocks), dim3(BLOCK), PLBM_FS_LDS, s, g.a);
-    hipLaunchKernelGGL(k_fs_mark_fill, dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
-    hipLaunchKernelGGL((k_fs_mark_empty<S>), dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
-    hipLaunchKernelGGL(k_fs_excess, dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
+    hipLaunchKernelGGL(k_fs_mark, dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
+    hipLaunchKernelGGL((k_fs_convert<S>), dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
     hipLaunchKernelGGL((k_fs_final<S>), dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
     if (g.blocksm) hipLaunchKernelGGL((k_fs_moments<S>), dim3(g.blocksm), dim3(BLOCK), 0, s, g.am);
 }
