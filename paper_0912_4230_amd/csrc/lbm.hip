@@ -440,6 +440,27 @@ bool diag_step(const lbm_sim *h, long long t, bool last)
     return last || (h->d.diag_every > 0 && t % h->d.diag_every == 0);
 }
 
+// Second stage of the diagnostics of n lattices (at most MAXB).
+void launch_diag(lbm_sim *const *hs, int n, hipStream_t s)
+{
+    BatchArgs a, c;
+    memset(&a, 0, sizeof(a));
+    memset(&c, 0, sizeof(c));
+    int chunks = 0;
+    for (int i = 0; i < n; ++i) {
+        a.lat[i] = hs[i]->dev;
+        const int nc = diag_chunks(hs[i]->nblocks);
+        if (!nc) continue;
+        c.blk_start[c.n] = chunks;
+        c.lat[c.n++] = hs[i]->dev;
+        chunks += nc;
+    }
+    c.blk_start[c.n] = chunks;
+    if (chunks) hipLaunchKernelGGL(k_diag_part, dim3(chunks), dim3(BLOCK), 0, s, c);
+    a.n = n;
+    hipLaunchKernelGGL(k_diag_final, dim3(n), dim3(BLOCK), 0, s, a);
+}
+
 // One batched step for lattices hs[0..n) of the same physics, storage and
 // permeability form (diagonal or full tensor):
 // [colour pass,] step kernel, [diagnostics second stage].
@@ -450,8 +471,7 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
     a.n = n;
     int total = 0;
     int ndiag = 0;
-    BatchArgs diag;
-    memset(&diag, 0, sizeof(diag));
+    lbm_sim *dhs[MAXB];
     for (int i = 0; i < n; ++i) {
         const lbm_sim *h = hs[i];
         // every lattice's range starts on a whole XCD row group (row_group_remap)
@@ -462,7 +482,7 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
         const bool dg = diag_step(h, t, last[i]);
         a.flags[i] = h->cur | (dg ? 2 : 0);
         a.nuc[i] = h->d.nu0 * time_factor(&h->d, double(t));
-        if (dg) diag.lat[ndiag++] = h->dev;
+        if (dg) dhs[ndiag++] = hs[i];
     }
     a.blk_start[n] = total;
     a.total_blocks = total;
@@ -515,10 +535,7 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
         if (h0->d.physics == LBM_IMMISCIBLE) colour_launcher(h0->d.storage)(a, total, h0->stream);
         step_launcher(h0->d.physics, h0->d.storage, h0->host.full_tensor != 0)(a, total, h0->stream);
     }
-    if (ndiag) {
-        diag.n = ndiag;
-        hipLaunchKernelGGL(k_diag_final, dim3(ndiag), dim3(BLOCK), 0, h0->stream, diag);
-    }
+    if (ndiag) launch_diag(dhs, ndiag, h0->stream);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return LBM_EDEVICE;
     for (int i = 0; i < n; ++i) {
@@ -863,11 +880,8 @@ lbm_status lbm_set_medium(lbm_t h, const lbm_medium *m)
     case LBM_MISCIBLE: init_for_storage<PH_MISCIBLE>(h, m, h->nblocks); break;
     default: init_for_storage<PH_IMMISCIBLE>(h, m, h->nblocks); break;
     }
-    BatchArgs diag;
-    memset(&diag, 0, sizeof(diag));
-    diag.n = 1;
-    diag.lat[0] = h->dev;
-    hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(BLOCK), 0, h->stream, diag);
+    lbm_sim *one[1] = {h};
+    launch_diag(one, 1, h->stream);
     if ((st = dev_err(hipGetLastError()))) return st;
     int err = 0;
     if ((st = dev_err(hipMemcpyAsync(&err, D.err, sizeof(int), hipMemcpyDeviceToHost, h->stream)))) return st;
@@ -1001,6 +1015,14 @@ lbm_status lbm_solute_totals(lbm_t h, double *totals)
         hipLaunchKernelGGL(k_solute_partials<double>, dim3(h->nblocks), dim3(BLOCK), 0, h->stream, (const LatDev *)h->dev, nsp);
     else
         hipLaunchKernelGGL(k_solute_partials<float>, dim3(h->nblocks), dim3(BLOCK), 0, h->stream, (const LatDev *)h->dev, nsp);
+    if (const int nc = diag_chunks(h->nblocks)) {
+        BatchArgs a;
+        memset(&a, 0, sizeof(a));
+        a.n = 1;
+        a.lat[0] = h->dev;
+        a.blk_start[1] = nc;
+        hipLaunchKernelGGL(k_diag_part, dim3(nc), dim3(BLOCK), 0, h->stream, a);
+    }
     hipLaunchKernelGGL(k_solute_final, dim3(1), dim3(BLOCK), 0, h->stream, (const LatDev *)h->dev, nsp);
     lbm_status st;
     if ((st = dev_err(hipGetLastError()))) return st;
