@@ -54,28 +54,29 @@ __host__ __device__ constexpr float weight<float>(int q)
 
 // ---------------------------------------------------------------------------
 // storage codecs: Codec<S>::R is the compute type, load/store convert.
-// Populations are streamed: each value is read once, one step after it was
-// written, long after it has left the caches, so both directions use the
-// non-temporal cache policy by default.
+//
+// Cache policy of the populations in a step.  Loads (NT): non-temporal, or plain.
+// Stores (WT): non-temporal, or written through to the memory side at once (a
+// relaxed store of agent scope), which leaves nothing dirty in the L2s for the
+// end of the launch and the values in the memory-side cache (256 MB).  The
+// launch chooses (lbm.hip: cache_policy, where both sides' times stand).
+enum {
+    CACHE_STREAM = 0,   // non-temporal loads and stores
+    CACHE_REUSE = 1,    // plain loads, non-temporal stores
+    CACHE_KEEP = 2      // plain loads, stores written through
+};
 
-#ifndef PLBM_NT_STORE
-#define PLBM_NT_STORE 1
-#endif
-#ifndef PLBM_NT_LOAD
-#define PLBM_NT_LOAD 1
-#endif
-
-template <class T>
+template <bool WT, class T>
 __device__ inline void st(GL T *p, T v)
 {
-    if constexpr (PLBM_NT_STORE) __builtin_nontemporal_store(v, p);
-    else *p = v;
+    if constexpr (WT) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else __builtin_nontemporal_store(v, p);
 }
 
-template <class T>
+template <bool NT, class T>
 __device__ inline T ld(const GL T *p)
 {
-    if constexpr (PLBM_NT_LOAD) return __builtin_nontemporal_load(p);
+    if constexpr (NT) return __builtin_nontemporal_load(p);
     else return *p;
 }
 
@@ -87,15 +88,15 @@ template <class S> struct Codec;
 template <> struct Codec<double> {
     using R = double;
     static constexpr bool split = false;
-    __device__ static R load(const GL double *p) { return ld(p); }
-    __device__ static void store(GL double *p, R v) { st(p, v); }
+    template <bool NT = true> __device__ static R load(const GL double *p) { return ld<NT>(p); }
+    template <bool WT = false> __device__ static void store(GL double *p, R v) { st<WT>(p, v); }
 };
 
 template <> struct Codec<float> {
     using R = float;
     static constexpr bool split = false;
-    __device__ static R load(const GL float *p) { return ld(p); }
-    __device__ static void store(GL float *p, R v) { st(p, v); }
+    template <bool NT = true> __device__ static R load(const GL float *p) { return ld<NT>(p); }
+    template <bool WT = false> __device__ static void store(GL float *p, R v) { st<WT>(p, v); }
 };
 
 // bfloat16: the upper half of an IEEE float; the hardware conversion
@@ -103,13 +104,13 @@ template <> struct Codec<float> {
 template <> struct Codec<bf16_t> {
     using R = float;
     static constexpr bool split = false;
-    __device__ static R load(const GL bf16_t *p)
+    template <bool NT = true> __device__ static R load(const GL bf16_t *p)
     {
-        return __uint_as_float(uint32_t(ld(reinterpret_cast<const GL uint16_t *>(p))) << 16);
+        return __uint_as_float(uint32_t(ld<NT>(reinterpret_cast<const GL uint16_t *>(p))) << 16);
     }
-    __device__ static void store(GL bf16_t *p, R v)
+    template <bool WT = false> __device__ static void store(GL bf16_t *p, R v)
     {
-        st(reinterpret_cast<GL uint16_t *>(p), __builtin_bit_cast(uint16_t, (__bf16)v));
+        st<WT>(reinterpret_cast<GL uint16_t *>(p), __builtin_bit_cast(uint16_t, (__bf16)v));
     }
 };
 
@@ -117,13 +118,13 @@ template <> struct Codec<bf16_t> {
 template <> struct Codec<f16_t> {
     using R = float;
     static constexpr bool split = false;
-    __device__ static R load(const GL f16_t *p)
+    template <bool NT = true> __device__ static R load(const GL f16_t *p)
     {
-        return float(__builtin_bit_cast(_Float16, ld(reinterpret_cast<const GL uint16_t *>(p))));
+        return float(__builtin_bit_cast(_Float16, ld<NT>(reinterpret_cast<const GL uint16_t *>(p))));
     }
-    __device__ static void store(GL f16_t *p, R v)
+    template <bool WT = false> __device__ static void store(GL f16_t *p, R v)
     {
-        st(reinterpret_cast<GL uint16_t *>(p), __builtin_bit_cast(uint16_t, _Float16(v)));
+        st<WT>(reinterpret_cast<GL uint16_t *>(p), __builtin_bit_cast(uint16_t, _Float16(v)));
     }
 };
 
@@ -140,32 +141,32 @@ struct f16s_t { uint16_t v; };
 template <> struct Codec<bf16s_t> {
     using R = float;
     static constexpr bool split = true;
-    __device__ static R load(const GL bf16s_t *p)
+    template <bool NT = true> __device__ static R load(const GL bf16s_t *p)
     {
         // Converting through the __bf16 type keeps this a plain 16-bit load
         // followed by a shift.  Written as an integer shift, the shift can be
         // folded into a load into the high half of a register (tied to that
         // register's old value), which serialised the split pulls.
-        return float(__builtin_bit_cast(__bf16, ld(reinterpret_cast<const GL uint16_t *>(p))));
+        return float(__builtin_bit_cast(__bf16, ld<NT>(reinterpret_cast<const GL uint16_t *>(p))));
     }
-    __device__ static void store(GL bf16s_t *p, R v) { Codec<bf16_t>::store(reinterpret_cast<GL bf16_t *>(p), v); }
+    template <bool WT = false> __device__ static void store(GL bf16s_t *p, R v) { Codec<bf16_t>::store<WT>(reinterpret_cast<GL bf16_t *>(p), v); }
     // the 16-bit word of v (rounded to nearest even) and its value
     __device__ static uint16_t enc(R v) { return __builtin_bit_cast(uint16_t, (__bf16)v); }
     __device__ static R dec(uint16_t b) { return float(__builtin_bit_cast(__bf16, b)); }
-    __device__ static void store_bits(GL bf16s_t *p, uint16_t b) { st(reinterpret_cast<GL uint16_t *>(p), b); }
+    template <bool WT = false> __device__ static void store_bits(GL bf16s_t *p, uint16_t b) { st<WT>(reinterpret_cast<GL uint16_t *>(p), b); }
 };
 
 template <> struct Codec<f16s_t> {
     using R = float;
     static constexpr bool split = true;
-    __device__ static R load(const GL f16s_t *p)
+    template <bool NT = true> __device__ static R load(const GL f16s_t *p)
     {
-        return Codec<f16_t>::load(reinterpret_cast<const GL f16_t *>(p));
+        return Codec<f16_t>::load<NT>(reinterpret_cast<const GL f16_t *>(p));
     }
-    __device__ static void store(GL f16s_t *p, R v) { Codec<f16_t>::store(reinterpret_cast<GL f16_t *>(p), v); }
+    template <bool WT = false> __device__ static void store(GL f16s_t *p, R v) { Codec<f16_t>::store<WT>(reinterpret_cast<GL f16_t *>(p), v); }
     __device__ static uint16_t enc(R v) { return __builtin_bit_cast(uint16_t, _Float16(v)); }
     __device__ static R dec(uint16_t b) { return float(__builtin_bit_cast(_Float16, b)); }
-    __device__ static void store_bits(GL f16s_t *p, uint16_t b) { st(reinterpret_cast<GL uint16_t *>(p), b); }
+    template <bool WT = false> __device__ static void store_bits(GL f16s_t *p, uint16_t b) { st<WT>(reinterpret_cast<GL uint16_t *>(p), b); }
 };
 
 // Paired 16-bit storage: the value of a link in both lattices of the
@@ -194,8 +195,8 @@ template <> struct PairCodec<bf16_t> {
         const bf16x2_t v = {(__bf16)a, (__bf16)b};
         return __builtin_bit_cast(uint32_t, v);
     }
-    __device__ static void load(const GL W *p, R &a, R &b) { decode(ld(p), a, b); }
-    __device__ static void store(GL W *p, R a, R b) { st(p, encode(a, b)); }
+    template <bool NT = true> __device__ static void load(const GL W *p, R &a, R &b) { decode(ld<NT>(p), a, b); }
+    template <bool WT = false> __device__ static void store(GL W *p, R a, R b) { st<WT>(p, encode(a, b)); }
 };
 
 template <> struct PairCodec<f16_t> {
@@ -212,8 +213,8 @@ template <> struct PairCodec<f16_t> {
         const f16x2_t v = {_Float16(a), _Float16(b)};
         return __builtin_bit_cast(uint32_t, v);
     }
-    __device__ static void load(const GL W *p, R &a, R &b) { decode(ld(p), a, b); }
-    __device__ static void store(GL W *p, R a, R b) { st(p, encode(a, b)); }
+    template <bool NT = true> __device__ static void load(const GL W *p, R &a, R &b) { decode(ld<NT>(p), a, b); }
+    template <bool WT = false> __device__ static void store(GL W *p, R a, R b) { st<WT>(p, encode(a, b)); }
 };
 
 // the split codecs pair their 16-bit remainders the same way (and their two

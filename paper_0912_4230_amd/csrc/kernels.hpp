@@ -348,21 +348,21 @@ constexpr int pair_lo() { return Q < opp(Q) ? Q : opp(Q); }
 // takes both from the cell itself.  BB = false: no cell of the wave has a
 // solid upstream neighbour.  XL: the masses of the links with c_x != 0 are
 // not loaded here (xl_masses).
-template <class S, bool BB, bool XL, int Q = 0>
+template <class S, bool BB, bool XL, bool NT, int Q = 0>
 __device__ inline void split_loads(const void *P, const void *M, uint32_t n, uint32_t idx, const Nbr &b,
                                    typename Codec<S>::R *r, typename Codec<S>::R *m)
 {
     using R = typename Codec<S>::R;
     if constexpr (BB && Q != 0) {
         const bool s = shifted_solid<Q, -1>(b);
-        r[Q] = Codec<S>::load(at(plane<S>(P, n, pair_lo<Q>()), pair_offset<Q>(b, n, idx, s)));
+        r[Q] = Codec<S>::template load<NT>(at(plane<S>(P, n, pair_lo<Q>()), pair_offset<Q>(b, n, idx, s)));
         m[Q] = ldg<R>(M, s ? idx : shifted<Q, -1>(b));
     } else {
         const uint32_t src = shifted<Q, -1>(b);
-        r[Q] = Codec<S>::load(at(plane<S>(P, n, Q), src));
+        r[Q] = Codec<S>::template load<NT>(at(plane<S>(P, n, Q), src));
         if constexpr (!XL || cx(Q) == 0) m[Q] = ldg<R>(M, src);
     }
-    if constexpr (Q + 1 < NQ) split_loads<S, BB, XL, Q + 1>(P, M, n, idx, b, r, m);
+    if constexpr (Q + 1 < NQ) split_loads<S, BB, XL, NT, Q + 1>(P, M, n, idx, b, r, m);
 }
 
 // Split codecs, waves without bounce-back: the upstream mass of a link with
@@ -485,7 +485,7 @@ __device__ inline void nb_shift(const XLanes &x, const R *e, R *v)
     if constexpr (Q + 1 < NQ) nb_shift<R, Q + 1>(x, e, v);
 }
 
-template <class S, bool BB, bool XL = false, int Q = 0>
+template <class S, bool BB, bool XL, bool NT, int Q = 0>
 __device__ inline void pull_each(const void *P, const void *M, uint32_t n, uint32_t idx, const Nbr &b,
                                  typename Codec<S>::R *out, const XLanes &xl = XLanes{})
 {
@@ -493,7 +493,7 @@ __device__ inline void pull_each(const void *P, const void *M, uint32_t n, uint3
     if constexpr (Codec<S>::split) {
         // all remainder and mass loads first, then the decode
         R r[NQ], m[NQ];
-        split_loads<S, BB, XL>(P, M, n, idx, b, r, m);
+        split_loads<S, BB, XL, NT>(P, M, n, idx, b, r, m);
         if constexpr (XL) {
             R e[NQ];
             xl_loads<R>(M, b, xl, e);
@@ -504,36 +504,36 @@ __device__ inline void pull_each(const void *P, const void *M, uint32_t n, uint3
     } else {
         if constexpr (BB && Q != 0) {
             const bool s = shifted_solid<Q, -1>(b);
-            out[Q] = Codec<S>::load(at(plane<S>(P, n, pair_lo<Q>()), pair_offset<Q>(b, n, idx, s)));
+            out[Q] = Codec<S>::template load<NT>(at(plane<S>(P, n, pair_lo<Q>()), pair_offset<Q>(b, n, idx, s)));
         } else {
-            out[Q] = Codec<S>::load(at(plane<S>(P, n, Q), shifted<Q, -1>(b)));
+            out[Q] = Codec<S>::template load<NT>(at(plane<S>(P, n, Q), shifted<Q, -1>(b)));
         }
-        if constexpr (Q + 1 < NQ) pull_each<S, BB, false, Q + 1>(P, M, n, idx, b, out);
+        if constexpr (Q + 1 < NQ) pull_each<S, BB, false, NT, Q + 1>(P, M, n, idx, b, out);
     }
 }
 
 // Pull of one lattice.  Waves without a solid upstream neighbour (all but a
 // thin layer next to walls and obstacles) take the path without selects (and
 // with the split codecs, XS, the one that shares the x-links' masses).
-template <class S, bool XS = true>
+template <class S, bool XS = true, bool NT = true>
 __device__ inline void pull_all(const void *P, const void *M, uint32_t n, uint32_t idx, const Nbr &b,
                                 typename Codec<S>::R *out)
 {
     if constexpr (Codec<S>::split && XS) {
         const XLanes xl = xlanes(b, idx);
-        if (wave_near_solid(b) || xl_general(xl)) pull_each<S, true>(P, M, n, idx, b, out);
-        else pull_each<S, false, true>(P, M, n, idx, b, out, xl);
+        if (wave_near_solid(b) || xl_general(xl)) pull_each<S, true, false, NT>(P, M, n, idx, b, out);
+        else pull_each<S, false, true, NT>(P, M, n, idx, b, out, xl);
     } else {
-        if (wave_near_solid(b)) pull_each<S, true>(P, M, n, idx, b, out);
-        else pull_each<S, false>(P, M, n, idx, b, out);
+        if (wave_near_solid(b)) pull_each<S, true, false, NT>(P, M, n, idx, b, out);
+        else pull_each<S, false, false, NT>(P, M, n, idx, b, out);
     }
 }
 
-template <class S, int Q = 0>
+template <class S, bool WT, int Q = 0>
 __device__ inline void store_each(void *P, uint32_t n, uint32_t idx, const typename Codec<S>::R *v)
 {
-    Codec<S>::store(at(plane_w<S>(P, n, Q), idx), v[Q]);
-    if constexpr (Q + 1 < NQ) store_each<S, Q + 1>(P, n, idx, v);
+    Codec<S>::template store<WT>(at(plane_w<S>(P, n, Q), idx), v[Q]);
+    if constexpr (Q + 1 < NQ) store_each<S, WT, Q + 1>(P, n, idx, v);
 }
 
 // Store the 19 populations of a cell.  Split codecs: with m = sum_q v_q in
@@ -545,7 +545,7 @@ __device__ inline void store_each(void *P, uint32_t n, uint32_t idx, const typen
 // resolution of a the two roundings drop about 2b with one sign.  The
 // correction moves every decoded population by w_q times the rounding sum
 // and leaves the momentum as it was (sum_q w_q v_q = 0).
-template <class S>
+template <class S, bool WT = false>
 __device__ inline void store_all(void *P, void *M, uint32_t n, uint32_t idx, const typename Codec<S>::R *v)
 {
     using R = typename Codec<S>::R;
@@ -558,11 +558,11 @@ __device__ inline void store_all(void *P, void *M, uint32_t n, uint32_t idx, con
         for (int q = 0; q < NQ; ++q) {
             const uint16_t e = Codec<S>::enc(fma(-weight<R>(q), m, v[q]));
             s += Codec<S>::dec(e);
-            Codec<S>::store_bits(at(plane_w<S>(P, n, q), idx), e);
+            Codec<S>::template store_bits<WT>(at(plane_w<S>(P, n, q), idx), e);
         }
         stg<R>(M, idx, m - s);
     } else {
-        store_each<S>(P, n, idx, v);
+        store_each<S, WT>(P, n, idx, v);
     }
 }
 
@@ -574,25 +574,25 @@ __device__ inline void store_all(void *P, void *M, uint32_t n, uint32_t idx, con
 template <int PHYS, class S>
 constexpr bool paired_v = PHYS == PH_MISCIBLE && sizeof(S) == 2;
 
-template <class S, bool BB, bool XL, int Q = 0>
+template <class S, bool BB, bool XL, bool NT, int Q = 0>
 __device__ inline void pair_loads(const void *P, const void *M, uint32_t n, uint32_t idx, const Nbr &b,
                                   typename Codec<S>::R *a, typename Codec<S>::R *c, f32x2_t *m)
 {
     using W = typename PairCodec<S>::W;
     if constexpr (BB && Q != 0) {
         const bool s = shifted_solid<Q, -1>(b);
-        PairCodec<S>::load(at(plane<W>(P, n, pair_lo<Q>()), pair_offset<Q>(b, n, idx, s)), a[Q], c[Q]);
+        PairCodec<S>::template load<NT>(at(plane<W>(P, n, pair_lo<Q>()), pair_offset<Q>(b, n, idx, s)), a[Q], c[Q]);
         if constexpr (Codec<S>::split) m[Q] = ldg<f32x2_t>(M, s ? idx : shifted<Q, -1>(b));
     } else {
         const uint32_t src = shifted<Q, -1>(b);
-        PairCodec<S>::load(at(plane<W>(P, n, Q), src), a[Q], c[Q]);
+        PairCodec<S>::template load<NT>(at(plane<W>(P, n, Q), src), a[Q], c[Q]);
         if constexpr (Codec<S>::split && (!XL || cx(Q) == 0)) m[Q] = ldg<f32x2_t>(M, src);
     }
-    if constexpr (Q + 1 < NQ) pair_loads<S, BB, XL, Q + 1>(P, M, n, idx, b, a, c, m);
+    if constexpr (Q + 1 < NQ) pair_loads<S, BB, XL, NT, Q + 1>(P, M, n, idx, b, a, c, m);
 }
 
 // Pull of both lattices from paired planes (a: f, c: h).
-template <class S>
+template <class S, bool NT = true>
 __device__ inline void pull_pair(const void *P, const void *M, uint32_t n, uint32_t idx, const Nbr &b,
                                  typename Codec<S>::R *a, typename Codec<S>::R *c)
 {
@@ -601,16 +601,16 @@ __device__ inline void pull_pair(const void *P, const void *M, uint32_t n, uint3
     if constexpr (Codec<S>::split) {
         const XLanes xl = xlanes(b, idx);
         if (wave_near_solid(b) || xl_general(xl)) {
-            pair_loads<S, true, false>(P, M, n, idx, b, a, c, m);
+            pair_loads<S, true, false, NT>(P, M, n, idx, b, a, c, m);
         } else {
-            pair_loads<S, false, true>(P, M, n, idx, b, a, c, m);
+            pair_loads<S, false, true, NT>(P, M, n, idx, b, a, c, m);
             f32x2_t e[NQ];
             xl_loads<f32x2_t>(M, b, xl, e);
             xl_masses<f32x2_t>(xl, e, m);
         }
     } else {
-        if (wave_near_solid(b)) pair_loads<S, true, false>(P, M, n, idx, b, a, c, m);
-        else pair_loads<S, false, false>(P, M, n, idx, b, a, c, m);
+        if (wave_near_solid(b)) pair_loads<S, true, false, NT>(P, M, n, idx, b, a, c, m);
+        else pair_loads<S, false, false, NT>(P, M, n, idx, b, a, c, m);
     }
     if constexpr (Codec<S>::split) {
 #pragma unroll
@@ -624,7 +624,7 @@ __device__ inline void pull_pair(const void *P, const void *M, uint32_t n, uint3
 // Store of both lattices' 19 populations into paired planes (split codecs:
 // the masses as in store_all, less the sums of the rounded remainders, one
 // pair per cell).
-template <class S>
+template <class S, bool WT = false>
 __device__ inline void store_pair(void *P, void *M, uint32_t n, uint32_t idx, const typename Codec<S>::R *a,
                                   const typename Codec<S>::R *c)
 {
@@ -645,12 +645,12 @@ __device__ inline void store_pair(void *P, void *M, uint32_t n, uint32_t idx, co
             PairCodec<S>::decode(wd, ta, tc);
             sa += ta;
             sc += tc;
-            st(at(plane_w<W>(P, n, q), idx), wd);
+            st<WT>(at(plane_w<W>(P, n, q), idx), wd);
         }
         stg<f32x2_t>(M, idx, f32x2_t{ma - sa, mc - sc});
     } else {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) PairCodec<S>::store(at(plane_w<W>(P, n, q), idx), a[q], c[q]);
+        for (int q = 0; q < NQ; ++q) PairCodec<S>::template store<WT>(at(plane_w<W>(P, n, q), idx), a[q], c[q]);
     }
 }
 
@@ -1167,12 +1167,13 @@ template <> struct StepWaves<PH_MISCIBLE, f16_t, false, false> { static constexp
 template <> struct StepWaves<PH_MISCIBLE, bf16s_t, false, false> { static constexpr int value = 4; };
 template <> struct StepWaves<PH_MISCIBLE, f16s_t, false, false> { static constexpr int value = 4; };
 
-template <int PHYS, class S, bool FT = false, bool MS = false>
+template <int PHYS, class S, bool FT = false, bool MS = false, int CP = CACHE_STREAM>
 __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, FT, MS>::value))) void k_step(
     const BatchArgs a)
 {
     using R = typename Codec<S>::R;
     constexpr bool HW = HwMath<S>::value;
+    constexpr bool NT = CP == CACHE_STREAM, WT = CP == CACHE_KEEP;
     const int gb = xcd_remap(blockIdx.x, a.total_blocks);
     const int l = find_lattice(a, gb);
     const LatDev *__restrict__ L = a.lat[l];
@@ -1215,10 +1216,10 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
     if (type == CELL_FLUID) {
         const Nbr b = neighbours(L, x, y, z, lw);
         if constexpr (paired_v<PHYS, S>) {
-            pull_pair<S>(L->f[src], L->fm[src], L->ppstride, idx, b, d, hq);
+            pull_pair<S, NT>(L->f[src], L->fm[src], L->ppstride, idx, b, d, hq);
         } else {
-            pull_all<S>(L->f[src], L->fm[src], L->pstride, idx, b, d);
-            if constexpr (PHYS == PH_MISCIBLE) pull_all<S>(L->h[src], L->hm[src], L->pstride, idx, b, hq);
+            pull_all<S, true, NT>(L->f[src], L->fm[src], L->pstride, idx, b, d);
+            if constexpr (PHYS == PH_MISCIBLE) pull_all<S, true, NT>(L->h[src], L->hm[src], L->pstride, idx, b, hq);
         }
 
         R drho = 0, jx = 0, jy = 0, jz = 0;
@@ -1353,10 +1354,10 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
     // waves made of solid cells only (wall planes, obstacle interiors) skip
     if (idx < ncell && __builtin_amdgcn_ballot_w64(type != CELL_SOLID) != 0) {
         if constexpr (paired_v<PHYS, S>) {
-            store_pair<S>(L->f[dst], L->fm[dst], L->ppstride, idx, d, hq);
+            store_pair<S, WT>(L->f[dst], L->fm[dst], L->ppstride, idx, d, hq);
         } else {
-            if constexpr (PHYS != PH_SINGLE) store_all<S>(L->h[dst], L->hm[dst], L->pstride, idx, hq);
-            store_all<S>(L->f[dst], L->fm[dst], L->pstride, idx, d);
+            if constexpr (PHYS != PH_SINGLE) store_all<S, WT>(L->h[dst], L->hm[dst], L->pstride, idx, hq);
+            store_all<S, WT>(L->f[dst], L->fm[dst], L->pstride, idx, d);
         }
     }
     if constexpr (MS) {
@@ -1375,7 +1376,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
                 Nbr bk = bx;
                 asm volatile("" : "+v"(bk.xm), "+v"(bk.x0), "+v"(bk.xp), "+v"(bk.ym), "+v"(bk.y0), "+v"(bk.yp),
                              "+v"(bk.zm), "+v"(bk.z0), "+v"(bk.zp), "+v"(bk.bb));
-                pull_all<S>(X->h[k][src], X->hm[k][src], L->pstride, idx, bk, hk);
+                pull_all<S, true, NT>(X->h[k][src], X->hm[k][src], L->pstride, idx, bk, hk);
                 R sh = 0;
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) sh += hk[q];
@@ -1394,7 +1395,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
                 for (int q = 0; q < NQ; ++q) hk[q] = R(0);
             }
             if (idx < ncell && __builtin_amdgcn_ballot_w64(type != CELL_SOLID) != 0)
-                store_all<S>(X->h[k][dst], X->hm[k][dst], L->pstride, idx, hk);
+                store_all<S, WT>(X->h[k][dst], X->hm[k][dst], L->pstride, idx, hk);
         }
     }
     if (mom) {
@@ -1408,7 +1409,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
 // computed (fluid cells: sum of the streamed g; reservoir cells: C_bc rho_bc;
 // solid cells: the wall colour (1 + cos theta)/2), which the step kernel
 // reads at the 18 neighbours for the colour gradient.
-template <class S>
+template <class S, int CP = CACHE_STREAM>
 __global__ __launch_bounds__(BLOCK) void k_colour(const BatchArgs a)
 {
     using R = typename Codec<S>::R;
@@ -1437,7 +1438,7 @@ __global__ __launch_bounds__(BLOCK) void k_colour(const BatchArgs a)
     } else {
         const Nbr b = neighbours(L, x, y, z, lw);
         R g[NQ];
-        pull_all<S>(L->h[src], L->hm[src], L->pstride, idx, b, g);
+        pull_all<S, true, CP == CACHE_STREAM>(L->h[src], L->hm[src], L->pstride, idx, b, g);
         v = 0;
 #pragma unroll
         for (int q = 0; q < NQ; ++q) v += g[q];

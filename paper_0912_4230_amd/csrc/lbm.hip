@@ -266,43 +266,80 @@ using Launch = void (*)(const BatchArgs &, int blocks, hipStream_t);
 // SIMD, which measured 2-3% slower on the FP32 miscible and two-fluid steps.
 constexpr size_t STEP_LDS_RESERVE = 33 * 1024;
 
-template <int P, class S, bool FT, bool MS = false>
+template <int P, class S, bool FT, bool MS, int CP>
 void launch_step(const BatchArgs &a, int blocks, hipStream_t s)
 {
     const size_t lds = StepWaves<P, S, FT, MS>::value == 5 ? 0 : STEP_LDS_RESERVE;
-    hipLaunchKernelGGL((k_step<P, S, FT, MS>), dim3(blocks), dim3(BLOCK), lds, s, a);
+    hipLaunchKernelGGL((k_step<P, S, FT, MS, CP>), dim3(blocks), dim3(BLOCK), lds, s, a);
 }
 
-template <class S>
+template <class S, int CP>
 void launch_colour(const BatchArgs &a, int blocks, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_colour<S>), dim3(blocks), dim3(BLOCK), 0, s, a);
+    hipLaunchKernelGGL((k_colour<S, CP>), dim3(blocks), dim3(BLOCK), 0, s, a);
 }
 
-template <int P, bool FT, bool MS = false>
+template <int P, bool FT, bool MS, int CP>
 Launch step_for_storage(int storage)
 {
     switch (storage) {
-    case LBM_F64: return launch_step<P, double, FT, MS>;
-    case LBM_F32: return launch_step<P, float, FT, MS>;
-    case LBM_BF16_DEV: return launch_step<P, bf16_t, FT, MS>;
-    case LBM_F16_DEV: return launch_step<P, f16_t, FT, MS>;
-    case LBM_BF16_SPLIT: return launch_step<P, bf16s_t, FT, MS>;
-    default: return launch_step<P, f16s_t, FT, MS>;
+    case LBM_F64: return launch_step<P, double, FT, MS, CP>;
+    case LBM_F32: return launch_step<P, float, FT, MS, CP>;
+    case LBM_BF16_DEV: return launch_step<P, bf16_t, FT, MS, CP>;
+    case LBM_F16_DEV: return launch_step<P, f16_t, FT, MS, CP>;
+    case LBM_BF16_SPLIT: return launch_step<P, bf16s_t, FT, MS, CP>;
+    default: return launch_step<P, f16s_t, FT, MS, CP>;
     }
 }
 
-template <int P>
-Launch step_for_tensor(int storage, bool full_tensor)
+// ms: miscible lattices with further solutes
+template <bool FT, int CP>
+Launch step_for_physics(int physics, int storage, bool ms)
 {
-    return full_tensor ? step_for_storage<P, true>(storage) : step_for_storage<P, false>(storage);
+    switch (physics) {
+    case LBM_SINGLE: return step_for_storage<PH_SINGLE, FT, false, CP>(storage);
+    case LBM_MISCIBLE:
+        return ms ? step_for_storage<PH_MISCIBLE, FT, true, CP>(storage)
+                  : step_for_storage<PH_MISCIBLE, FT, false, CP>(storage);
+    default: return step_for_storage<PH_IMMISCIBLE, FT, false, CP>(storage);
+    }
 }
 
-// miscible lattices with further solutes
-Launch step_for_species(int storage, bool full_tensor)
+template <int CP>
+Launch step_for_cache(int physics, int storage, bool full_tensor, bool ms)
 {
-    return full_tensor ? step_for_storage<PH_MISCIBLE, true, true>(storage)
-                       : step_for_storage<PH_MISCIBLE, false, true>(storage);
+    return full_tensor ? step_for_physics<true, CP>(physics, storage, ms) : step_for_physics<false, CP>(physics, storage, ms);
+}
+
+Launch step_launcher(int physics, int storage, bool full_tensor, bool ms, int cache)
+{
+    switch (cache) {
+    case CACHE_REUSE: return step_for_cache<CACHE_REUSE>(physics, storage, full_tensor, ms);
+    case CACHE_KEEP: return step_for_cache<CACHE_KEEP>(physics, storage, full_tensor, ms);
+    default: return step_for_cache<CACHE_STREAM>(physics, storage, full_tensor, ms);
+    }
+}
+
+template <int CP>
+Launch colour_for_storage(int storage)
+{
+    switch (storage) {
+    case LBM_F64: return launch_colour<double, CP>;
+    case LBM_F32: return launch_colour<float, CP>;
+    case LBM_BF16_DEV: return launch_colour<bf16_t, CP>;
+    case LBM_F16_DEV: return launch_colour<f16_t, CP>;
+    case LBM_BF16_SPLIT: return launch_colour<bf16s_t, CP>;
+    default: return launch_colour<f16s_t, CP>;
+    }
+}
+
+Launch colour_launcher(int storage, int cache)
+{
+    switch (cache) {
+    case CACHE_REUSE: return colour_for_storage<CACHE_REUSE>(storage);
+    case CACHE_KEEP: return colour_for_storage<CACHE_KEEP>(storage);
+    default: return colour_for_storage<CACHE_STREAM>(storage);
+    }
 }
 
 // Free surface: the stream/collide pass on the step grid (a), the class
@@ -352,27 +389,6 @@ FsLaunch fs_launcher(int storage, bool full_tensor, bool st)
 {
     if (st) return full_tensor ? fs_for_storage<true, true>(storage) : fs_for_storage<false, true>(storage);
     return full_tensor ? fs_for_storage<true, false>(storage) : fs_for_storage<false, false>(storage);
-}
-
-Launch step_launcher(int physics, int storage, bool full_tensor)
-{
-    switch (physics) {
-    case LBM_SINGLE: return step_for_tensor<PH_SINGLE>(storage, full_tensor);
-    case LBM_MISCIBLE: return step_for_tensor<PH_MISCIBLE>(storage, full_tensor);
-    default: return step_for_tensor<PH_IMMISCIBLE>(storage, full_tensor);
-    }
-}
-
-Launch colour_launcher(int storage)
-{
-    switch (storage) {
-    case LBM_F64: return launch_colour<double>;
-    case LBM_F32: return launch_colour<float>;
-    case LBM_BF16_DEV: return launch_colour<bf16_t>;
-    case LBM_F16_DEV: return launch_colour<f16_t>;
-    case LBM_BF16_SPLIT: return launch_colour<bf16s_t>;
-    default: return launch_colour<f16s_t>;
-    }
 }
 
 template <int P, class S>
@@ -438,6 +454,63 @@ void init_for_storage(const lbm_sim *h, const lbm_medium *m, int blocks)
 bool diag_step(const lbm_sim *h, long long t, bool last)
 {
     return last || (h->d.diag_every > 0 && t % h->d.diag_every == 0);
+}
+
+// Cache policy of the populations in a step of these lattices (results are
+// bitwise the same under all three).  us per step, FP32 miscible unless named,
+// CACHE_STREAM / CACHE_REUSE / CACHE_KEEP:
+//
+// KEEP, when all the launch's populations (both copies) fit in the memory-side
+// cache (256 MB): a step then reads what the last one left there, where
+// non-temporal stores send it to memory.
+//   61^3 (69 MB) 15.4 / 15.7 / 13.6, 83^3 (174 MB) 40 / 39 / 32.6, 94^3 (252 MB)
+//   57 / 56 / 46, 98^3 (286 MB) 66 / 63 / 67; 70^3 BF16 (52 MB) 15.3 / 16.1 /
+//   14.4, 110^3 BF16 (202 MB) 47 / 46 / 41, 120^3 BF16 (263 MB) 59 / 57 / 60;
+//   two-fluid 80^3 36 / 37 / 30; channel FP64 64^3 17 / 18 / 14.
+// Lattices that the L2s (32 MB) hold in part step as fast or faster under STREAM:
+//   48^3 9.6 / 10.2 / 10.7, 58^3 12.0 / 13.4 / 12.6, 64^3 BF16 9.2 / 10.5 / 10.4;
+// the line lies at 62 MB in the miscible model in FP32 and FP64 (96 MB with rows
+// of whole lines: 64^3, 80 MB, 14.4 / 15.9 / 14.8), at 50 MB else.  The smallest
+// gain again (32^3 FP64 channel, 10 MB, 6.6 / 6.6 / 6.0; 64^3 BF16 channel, 20
+// MB, 8.0 / 7.3 / 7.0; miscible 32^3, 10 MB, 7.9 / 7.9 / 7.7, but 40^3, 20 MB,
+// 8.3 / 8.9 / 9.0).
+//
+// REUSE, when lines are read by two waves: rows that are not whole lines put
+// most lines across a wave boundary (243 x 251 x 238 970 / 935, tensor 1075 /
+// 997; 250^3 988 / 936; 131^3 two-fluid 142 / 135, BF16 93 / 87; channel 150^3
+// FP64 201 / 190; where rows are whole lines 256^3 945 / 970, 128^3 two-fluid
+// 122 / 128); bounced links read a line once more (10% obstacles 256^3 1120 /
+// 1035, BF16 567 / 553).  The paired 16-bit planes of the miscible model gain
+// only where rows are not whole sectors of 32 bytes (tensor 243 x 251 x 238 BF16
+// 560 / 544; 200^3 BF16 254 / 255), the split forms hardly (590 / 583; 211 x 190
+// x 177 BF16 split 271 / 274).  The FP32 tensor step
+// gains with whole lines too (256^3 1029 / 1008; BF16 590 / 600).
+//
+// The lattices of a batch share the launch: their bytes add up, and the larger
+// part of their cells decides between REUSE and STREAM.
+int cache_policy(lbm_sim *const *hs, int n)
+{
+    constexpr double MB = 1e6;
+    double bytes = 0, cells = 0, reuse = 0;
+    bool whole_lines = true;
+    for (int i = 0; i < n; ++i) {
+        const lbm_desc *d = &hs[i]->d;
+        const bool paired = paired_storage(d);
+        const size_t row = (size_t)d->nx * storage_bytes(d->storage) * (paired ? 2 : 1);
+        whole_lines = whole_lines && row % 128 == 0;
+        bytes += double(hs[i]->lay.total - hs[i]->lay.f0);
+        cells += hs[i]->host.ncell;
+        const bool shared = row % (paired ? 32 : 128) != 0 || hs[i]->host.links;
+        if (paired ? shared && !split_storage(d->storage)
+                   : shared || (hs[i]->host.full_tensor && d->storage == LBM_F32))
+            reuse += hs[i]->host.ncell;
+    }
+    const lbm_desc *d0 = &hs[0]->d;
+    const bool wide = d0->physics == LBM_MISCIBLE && !paired_storage(d0);
+    const double tiny = d0->physics == LBM_SINGLE ? 24 * MB : 12 * MB;
+    const double low = wide ? (whole_lines ? 96 * MB : 62 * MB) : 50 * MB;
+    if (bytes <= tiny || (bytes >= low && bytes <= 256 * MB)) return CACHE_KEEP;
+    return bytes > low && 2 * reuse > cells ? CACHE_REUSE : CACHE_STREAM;
 }
 
 // Second stage of the diagnostics of n lattices (at most MAXB).
@@ -529,11 +602,12 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
         bool st = false;
         for (int i = 0; i < n; ++i) st = st || hs[i]->d.A != 0.0;
         fs_launcher(h0->d.storage, h0->host.full_tensor != 0, st)(g, h0->stream);
-    } else if (h0->host.ms) {
-        step_for_species(h0->d.storage, h0->host.full_tensor != 0)(a, total, h0->stream);
     } else {
-        if (h0->d.physics == LBM_IMMISCIBLE) colour_launcher(h0->d.storage)(a, total, h0->stream);
-        step_launcher(h0->d.physics, h0->d.storage, h0->host.full_tensor != 0)(a, total, h0->stream);
+        const int cache = cache_policy(hs, n);
+        if (h0->d.physics == LBM_IMMISCIBLE)
+            colour_launcher(h0->d.storage, cache)(a, total, h0->stream);
+        step_launcher(h0->d.physics, h0->d.storage, h0->host.full_tensor != 0, h0->host.ms != nullptr, cache)(
+            a, total, h0->stream);
     }
     if (ndiag) launch_diag(dhs, ndiag, h0->stream);
     const hipError_t e = hipGetLastError();
