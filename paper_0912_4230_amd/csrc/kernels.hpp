@@ -27,6 +27,10 @@
 
 namespace plbm {
 
+// weight classes: rest, axes, diagonals; a link of each
+constexpr int weight_class(int q) { return q == 0 ? 0 : (q <= 6 ? 1 : 2); }
+constexpr int class_link(int k) { return k == 0 ? 0 : (k == 1 ? 1 : 7); }
+
 enum { PH_SINGLE = 0, PH_MISCIBLE = 1, PH_IMMISCIBLE = 2, PH_FREESURF = 3 };
 enum { CELL_FLUID = 0, CELL_SOLID = 1, CELL_RES = 2 };
 
@@ -1167,6 +1171,23 @@ template <> struct StepWaves<PH_MISCIBLE, f16_t, false, false> { static constexp
 template <> struct StepWaves<PH_MISCIBLE, bf16s_t, false, false> { static constexpr int value = 4; };
 template <> struct StepWaves<PH_MISCIBLE, f16s_t, false, false> { static constexpr int value = 4; };
 
+// AllLanes: a wave with a fluid cell runs the update in all of its lanes,
+// straight through.  The addresses of the lanes that are not fluid are in the
+// box (neighbours wraps every cell), and what they compute is replaced
+// afterwards in the waves that have such lanes.  With the update under a branch
+// of the fluid lanes, every wave moves the populations through registers where
+// its results merge with the reservoirs' and the solid cells' values (125 of
+// the 830 VALU instructions a BF16 miscible wave executes).  us per step,
+// branch / all lanes: channel 160^3 BF16 73.3 / 66.0, 64^3 BF16 7.9 / 7.4, 200^3
+// FP16 split 147.5 / 144; two-fluid 128^3 BF16 81 / 77, FP32 and FP64 the same;
+// two solutes 256^3 BF16 850 / 791 (FP16 split 690 / 708).  The miscible step
+// with one solute keeps the branch: without it the 16-bit deviations spill at
+// 5 waves (476 / 532) and the split forms lose 3% (616 / 634); FP32 gains 1% at
+// 256^3 and loses it with obstacles.
+template <int PHYS, class S, bool FT, bool MS> struct AllLanes {
+    static constexpr bool value = PHYS != PH_MISCIBLE || (MS && sizeof(S) == 2 && !Codec<S>::split);
+};
+
 template <int PHYS, class S, bool FT = false, bool MS = false, int CP = CACHE_STREAM>
 __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, FT, MS>::value))) void k_step(
     const BatchArgs a)
@@ -1174,6 +1195,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
     using R = typename Codec<S>::R;
     constexpr bool HW = HwMath<S>::value;
     constexpr bool NT = CP == CACHE_STREAM, WT = CP == CACHE_KEEP;
+    constexpr bool ALL = AllLanes<PHYS, S, FT, MS>::value;
     const int gb = xcd_remap(blockIdx.x, a.total_blocks);
     const int l = find_lattice(a, gb);
     const LatDev *__restrict__ L = a.lat[l];
@@ -1185,23 +1207,26 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
     const R nuc = R(a.nuc[l]);
 
     const uint32_t ncell = L->ncell;
-    const uint32_t idx = uint32_t(lb) * BLOCK + threadIdx.x;
+    uint32_t idx = uint32_t(lb) * BLOCK + threadIdx.x;
+    const bool in = idx < ncell;
     const uint32_t nx = L->nx, nxy = nx * uint32_t(L->ny);
-
-    // moments kept for the diagnostics of this step
-    bool has = false;
-    R m_rho = 0, m_C = 0, m_s4 = 0, m_u[3] = {0, 0, 0}, m_up[3] = {0, 0, 0};
     int type = CELL_SOLID;
     int x = 0, y = 0, z = 0, face = -1;
     uint32_t lw = 0;
-    if (idx < ncell) {
+    if constexpr (ALL) idx = in ? idx : ncell - 1;   // lanes beyond the last cell read its neighbours and store nothing
+    if (ALL || in) {
         z = udiv(idx, L->div_nxy);
         const uint32_t r = idx - uint32_t(z) * nxy;
         y = udiv(r, L->div_nx);
         x = r - uint32_t(y) * nx;
         lw = link_word(L, idx);
         type = cell_type(L, x, y, z, lw, face);
+        if constexpr (ALL) type = in ? type : CELL_SOLID;
     }
+    const bool fluid = type == CELL_FLUID;
+    // moments kept for the diagnostics of this step
+    bool has = false;
+    R m_rho = 0, m_C = 0, m_s4 = 0, m_u[3] = {0, 0, 0}, m_up[3] = {0, 0, 0};
     // Post-collision populations of both lattices.  Every cell of the box
     // stores them: fluid cells their update, reservoir cells their fixed
     // state (bitwise the set-up values), solid cells zeros.  Lanes that
@@ -1210,11 +1235,12 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
     // measured up to 30% slower (narrow rows) than the extra bytes.
     R d[NQ], hq[NQ];
     const int dst = src ^ 1;
-    // what the further solutes take from the fluid branch
+    // what the further solutes take from the update
     [[maybe_unused]] Nbr bx{};
     [[maybe_unused]] R x_eps = 1, x_ie = 1, x_u[3] = {0, 0, 0}, x_g[3] = {0, 0, 0};
-    if (type == CELL_FLUID) {
-        const Nbr b = neighbours(L, x, y, z, lw);
+    if (ALL ? __builtin_amdgcn_ballot_w64(fluid) != 0 : fluid) {
+        Nbr b = neighbours(L, x, y, z, lw);
+        if constexpr (ALL) b.bb = fluid ? b.bb : 0u;
         if constexpr (paired_v<PHYS, S>) {
             pull_pair<S, NT>(L->f[src], L->fm[src], L->ppstride, idx, b, d, hq);
         } else {
@@ -1225,7 +1251,9 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
         R drho = 0, jx = 0, jy = 0, jz = 0;
         moments_acc<R>(d, drho, jx, jy, jz);
         const R rho = R(1) + drho;
-        const R irho = rcp<HW>(rho);
+        // V = 0 in the lanes that are not fluid: what they pulled would keep the
+        // wave in the Newton iterations of the drag
+        const R irho = !ALL || fluid ? rcp<HW>(rho) : R(0);
         const R V[3] = {jx * irho, jy * irho, jz * irho};
 
         const R eps = L->uniform_eps ? R(L->eps_u) : ldg<R>(L->eps, idx);
@@ -1315,7 +1343,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
             recolour<R>(hq, d, C, Cw, rw, F);
         }
 
-        if (mom) {
+        if (mom && (!ALL || fluid)) {
             void *M = L->mom;
             const R up[3] = {ldp<R>(M, ncell, 1, idx), ldp<R>(M, ncell, 2, idx), ldp<R>(M, ncell, 3, idx)};
             stg<R>(M, idx, rho);
@@ -1332,7 +1360,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
                 m_up[k] = up[k];
             }
         }
-    } else if (type == CELL_RES) {
+    } else if (!ALL && type == CELL_RES) {
         // the fixed reservoir state, as set up: f^eq(rho_bc, V' = 0) and
         // h^eq(eps C_bc, 0) or g = C_bc f
         // rho_bc - 1 is formed in double before rounding (1 + 3 x 0.0441 in
@@ -1347,12 +1375,36 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
             d[q] = w * drb;
             hq[q] = PHYS == PH_MISCIBLE ? w * eps * cb : (PHYS == PH_IMMISCIBLE ? cb * w * rb : R(0));
         }
-    } else {
+    } else if (!ALL) {
 #pragma unroll
         for (int q = 0; q < NQ; ++q) d[q] = hq[q] = R(0);
     }
+    if constexpr (ALL) {
+        // the same values for the other lanes of a wave that has some: one per
+        // weight class, taken by a select for every population
+        if (__builtin_amdgcn_ballot_w64(!fluid) != 0) {
+            R fd[3] = {0, 0, 0}, fh[3] = {0, 0, 0};
+            if (type == CELL_RES) {
+                const R rb = R(L->face_rho[face]), cb = R(L->face_conc[face]), drb = R(L->face_rho[face] - 1.0);
+                R eps = R(1);
+                if constexpr (PHYS == PH_MISCIBLE) eps = L->uniform_eps ? R(L->eps_u) : ldg<R>(L->eps, idx);
+                if constexpr (MS) x_eps = eps;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const R w = weight<R>(class_link(k));
+                    fd[k] = w * drb;
+                    fh[k] = PHYS == PH_MISCIBLE ? w * eps * cb : (PHYS == PH_IMMISCIBLE ? cb * w * rb : R(0));
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                d[q] = fluid ? d[q] : fd[weight_class(q)];
+                if constexpr (PHYS != PH_SINGLE) hq[q] = fluid ? hq[q] : fh[weight_class(q)];
+            }
+        }
+    }
     // waves made of solid cells only (wall planes, obstacle interiors) skip
-    if (idx < ncell && __builtin_amdgcn_ballot_w64(type != CELL_SOLID) != 0) {
+    if ((ALL ? in : idx < ncell) && __builtin_amdgcn_ballot_w64(type != CELL_SOLID) != 0) {
         if constexpr (paired_v<PHYS, S>) {
             store_pair<S, WT>(L->f[dst], L->fm[dst], L->ppstride, idx, d, hq);
         } else {
@@ -1367,7 +1419,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
         const int nsx = X ? X->nsx : 0;
         for (int k = 0; k < nsx; ++k) {
             R hk[NQ];
-            if (type == CELL_FLUID) {
+            if (ALL ? __builtin_amdgcn_ballot_w64(fluid) != 0 : fluid) {
                 // an opaque copy of the neighbour offsets: without it the
                 // compiler hoists the 18 (split codecs: 36) per-link byte
                 // offsets out of the loop and keeps them live across it (split
@@ -1385,16 +1437,27 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(StepWaves<PHYS, S, 
                 const R omd = fdiv<HW>(R(1), R(X->tau_d[k]));
                 const R H[3] = {omd * weight<R>(0) * sh, omd * weight<R>(1) * sh, omd * weight<R>(7) * sh};
                 collide_h<R>(hk, R(1) - omd, H, vs);
-                if (mom) stp<R>(L->mom, ncell, 5 + k, idx, sh * x_ie);
-            } else if (type == CELL_RES) {
+                if (mom && (!ALL || fluid)) stp<R>(L->mom, ncell, 5 + k, idx, sh * x_ie);
+            } else if (!ALL && type == CELL_RES) {
                 const R cb = R(X->face_conc[k][face]);
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) hk[q] = weight<R>(q) * x_eps * cb;
-            } else {
+            } else if (!ALL) {
 #pragma unroll
                 for (int q = 0; q < NQ; ++q) hk[q] = R(0);
             }
-            if (idx < ncell && __builtin_amdgcn_ballot_w64(type != CELL_SOLID) != 0)
+            if constexpr (ALL) {
+                if (__builtin_amdgcn_ballot_w64(!fluid) != 0) {
+                    R fh[3] = {0, 0, 0};
+                    if (type == CELL_RES) {
+                        const R cb = R(X->face_conc[k][face]);
+                        for (int c = 0; c < 3; ++c) fh[c] = weight<R>(class_link(c)) * x_eps * cb;
+                    }
+#pragma unroll
+                    for (int q = 0; q < NQ; ++q) hk[q] = fluid ? hk[q] : fh[weight_class(q)];
+                }
+            }
+            if ((ALL ? in : idx < ncell) && __builtin_amdgcn_ballot_w64(type != CELL_SOLID) != 0)
                 store_all<S, WT>(X->h[k][dst], X->hm[k][dst], L->pstride, idx, hk);
         }
     }
