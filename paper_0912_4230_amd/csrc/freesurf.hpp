@@ -83,10 +83,8 @@ __device__ inline void fs_list_row(const GL FsDev *F, int buf, uint32_t row, uin
 // The free-surface block lives in the workspace (global memory); naming its
 // address space lets the compiler read its fields with scalar loads instead
 // of a vector round trip per field.
-__device__ inline const GL FsDev *fs_of(const LatDev *L)
-{
-    return static_cast<const GL FsDev *>((const GL void *)L->fs);
-}
+__device__ inline const GL FsDev *fs_block(const void *p) { return static_cast<const GL FsDev *>((const GL void *)p); }
+__device__ inline const GL FsDev *fs_of(const LatDev *L) { return fs_block(L->fs); }
 
 // f(std::integral_constant<int, Q>) for Q = 1 .. 18
 template <int Q = 1, class Fn>
@@ -174,12 +172,12 @@ __device__ inline FsCell fs_cell(const BatchArgs &a)
     FsCell c;
     const int gb = xcd_remap(blockIdx.x, a.total_blocks);
     c.l = find_lattice(a, gb);
-    c.L = a.lat[c.l];
-    c.F = fs_of(c.L);
+    c.L = a.e[c.l].lat;
+    c.F = fs_block(a.e[c.l].fs);
     // the pass-1 grid of a lattice (listed-row prefix + one block per row) is
     // not a whole number of planes: no slab or row-group remapping here
-    c.lb = gb - a.blk_start[c.l];
-    c.flags = a.flags[c.l];
+    c.lb = gb - a.e[c.l].first;
+    c.flags = a.e[c.l].flags;
     c.ncell = c.L->ncell;
     c.idx = uint32_t(c.lb) * BLOCK + threadIdx.x;
     return c;
@@ -244,7 +242,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>:
     const GL FsDev *__restrict__ F = c.F;
     const int src = c.flags & 1, dst = src ^ 1;
     const uint32_t nrow = (c.ncell + BLOCK - 1) / BLOCK;
-    const uint32_t cap = uint32_t(a.blk_start[c.l + 1] - a.blk_start[c.l]) - nrow;
+    const uint32_t cap = uint32_t(a.e[c.l].end - a.e[c.l].first) - nrow;
     const bool prefix = uint32_t(c.lb) < cap;
     uint32_t row;
     if (prefix) {
@@ -260,7 +258,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>:
     c.idx = row * BLOCK + threadIdx.x;
     const uint32_t idx = c.idx, ncell = c.ncell;
     const bool mom = (c.flags & 2) != 0;
-    const R nuc = R(a.nuc[c.l]);
+    const R nuc = R(a.e[c.l].nuc);
 
     int cls = FS_SOLID, x = 0, y = 0, z = 0;
     uint32_t lw = 0;
@@ -468,11 +466,11 @@ __device__ inline FsTile fs_tile(const BatchArgs &a)
     FsTile t;
     const int gb = blockIdx.x;
     const int l = find_lattice(a, gb);
-    t.L = a.lat[l];
-    t.F = fs_of(t.L);
-    t.flags = a.flags[l];
+    t.L = a.e[l].lat;
+    t.F = fs_block(a.e[l].fs);
+    t.flags = a.e[l].flags;
     t.ncell = t.L->ncell;
-    t.base = (uint32_t(gb - a.blk_start[l]) * BLOCK + threadIdx.x) * FS_CPT;
+    t.base = (uint32_t(gb - a.e[l].first) * BLOCK + threadIdx.x) * FS_CPT;
     return t;
 }
 

@@ -351,7 +351,6 @@ int fs_prefix_blocks(int rows) { return std::min(rows, std::max(64, rows / 32));
 
 struct FsGrids {
     BatchArgs a, a16, am;
-    int blocks, blocks16, blocksm;
 };
 
 #ifndef PLBM_FS_LDS
@@ -361,11 +360,11 @@ struct FsGrids {
 template <class S, bool FT, bool ST>
 void launch_fs(const FsGrids &g, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_fs_step<S, FT, ST>), dim3(g.blocks), dim3(BLOCK), PLBM_FS_LDS, s, g.a);
-    hipLaunchKernelGGL(k_fs_mark, dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
-    hipLaunchKernelGGL((k_fs_convert<S>), dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
-    hipLaunchKernelGGL((k_fs_final<S>), dim3(g.blocks16), dim3(BLOCK), 0, s, g.a16);
-    if (g.blocksm) hipLaunchKernelGGL((k_fs_moments<S>), dim3(g.blocksm), dim3(BLOCK), 0, s, g.am);
+    hipLaunchKernelGGL((k_fs_step<S, FT, ST>), dim3(g.a.total_blocks), dim3(BLOCK), PLBM_FS_LDS, s, g.a);
+    hipLaunchKernelGGL(k_fs_mark, dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
+    hipLaunchKernelGGL((k_fs_convert<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
+    hipLaunchKernelGGL((k_fs_final<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
+    if (g.am.n) hipLaunchKernelGGL((k_fs_moments<S>), dim3(g.am.n), dim3(BLOCK), 0, s, g.am);
 }
 
 using FsLaunch = void (*)(const FsGrids &, hipStream_t);
@@ -513,101 +512,75 @@ int cache_policy(lbm_sim *const *hs, int n)
     return bytes > low && 2 * reuse > cells ? CACHE_REUSE : CACHE_STREAM;
 }
 
+// Lattice h takes the next `blocks` blocks of the launch a.
+void add_lattice(BatchArgs &a, const lbm_sim *h, int blocks, int flags = 0, double nuc = 0.0)
+{
+    BatchEntry &e = a.e[a.n++];
+    e.lat = h->dev;
+    e.fs = h->host.fs;
+    e.nuc = nuc;
+    e.first = a.total_blocks;
+    e.end = a.total_blocks += blocks;
+    e.flags = flags;
+    e.pad = 0;
+}
+
 // Second stage of the diagnostics of n lattices (at most MAXB).
 void launch_diag(lbm_sim *const *hs, int n, hipStream_t s)
 {
     BatchArgs a, c;
-    memset(&a, 0, sizeof(a));
-    memset(&c, 0, sizeof(c));
-    int chunks = 0;
+    a.n = a.total_blocks = c.n = c.total_blocks = 0;
     for (int i = 0; i < n; ++i) {
-        a.lat[i] = hs[i]->dev;
-        const int nc = diag_chunks(hs[i]->nblocks);
-        if (!nc) continue;
-        c.blk_start[c.n] = chunks;
-        c.lat[c.n++] = hs[i]->dev;
-        chunks += nc;
+        add_lattice(a, hs[i], 1);
+        if (const int nc = diag_chunks(hs[i]->nblocks)) add_lattice(c, hs[i], nc);
     }
-    c.blk_start[c.n] = chunks;
-    if (chunks) hipLaunchKernelGGL(k_diag_part, dim3(chunks), dim3(BLOCK), 0, s, c);
-    a.n = n;
+    if (c.n) hipLaunchKernelGGL(k_diag_part, dim3(c.total_blocks), dim3(BLOCK), 0, s, c);
     hipLaunchKernelGGL(k_diag_final, dim3(n), dim3(BLOCK), 0, s, a);
 }
 
 // One batched step for lattices hs[0..n) of the same physics, storage and
 // permeability form (diagonal or full tensor):
-// [colour pass,] step kernel, [diagnostics second stage].
+// [colour pass,] step kernel, [diagnostics second stage].  The entries beyond n
+// of the arguments are not set: no kernel reads them.
 lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
 {
-    BatchArgs a;
-    memset(&a, 0, sizeof(a));
-    a.n = n;
-    int total = 0;
-    int ndiag = 0;
+    const lbm_sim *h0 = hs[0];
+    int flags[MAXB];
+    double nuc[MAXB];
     lbm_sim *dhs[MAXB];
+    int ndiag = 0;
     for (int i = 0; i < n; ++i) {
         const lbm_sim *h = hs[i];
-        // every lattice's range starts on a whole XCD row group (row_group_remap)
-        a.blk_start[i] = total;
-        total += (h->nblocks + XCD_GROUP - 1) / XCD_GROUP * XCD_GROUP;
-        a.lat[i] = h->dev;
         const long long t = h->steps + 1;
         const bool dg = diag_step(h, t, last[i]);
-        a.flags[i] = h->cur | (dg ? 2 : 0);
-        a.nuc[i] = h->d.nu0 * time_factor(&h->d, double(t));
+        flags[i] = h->cur | (dg ? 2 : 0);
+        nuc[i] = h->d.nu0 * time_factor(&h->d, double(t));
         if (dg) dhs[ndiag++] = hs[i];
     }
-    a.blk_start[n] = total;
-    a.total_blocks = total;
-    const lbm_sim *h0 = hs[0];
     if (h0->d.physics == LBM_FREESURF) {
         // pass 1: per lattice a prefix of blocks for the rows listed as
         // holding interface cells, then one block per row
         FsGrids g;
-        g.a = a;
-        int tp = 0;
-        for (int i = 0; i < n; ++i) {
-            g.a.blk_start[i] = tp;
-            tp += fs_prefix_blocks(hs[i]->nblocks) + hs[i]->nblocks;
-        }
-        g.a.blk_start[n] = tp;
-        g.a.total_blocks = tp;
-        g.blocks = tp;
-        memset(&g.a16, 0, sizeof(g.a16));
-        memset(&g.am, 0, sizeof(g.am));
-        int t16 = 0, tm = 0, nm = 0;
+        g.a.n = g.a.total_blocks = g.a16.n = g.a16.total_blocks = g.am.n = g.am.total_blocks = 0;
+        bool st = false;
         for (int i = 0; i < n; ++i) {
             const lbm_sim *h = hs[i];
-            const int nb16 = (h->host.ncell + BLOCK * FS_CPT - 1) / (BLOCK * FS_CPT);
-            g.a16.blk_start[i] = t16;
-            g.a16.lat[i] = h->dev;
-            g.a16.flags[i] = a.flags[i];
-            t16 += nb16;
-            if (a.flags[i] & 2) {
-                g.am.blk_start[nm] = tm;
-                g.am.lat[nm] = h->dev;
-                g.am.flags[nm] = a.flags[i];
-                tm += h->nblocks;
-                ++nm;
-            }
+            add_lattice(g.a, h, fs_prefix_blocks(h->nblocks) + h->nblocks, flags[i], nuc[i]);
+            add_lattice(g.a16, h, (h->host.ncell + BLOCK * FS_CPT - 1) / (BLOCK * FS_CPT), flags[i]);
+            if (flags[i] & 2) add_lattice(g.am, h, h->nblocks, flags[i]);
+            st = st || h->d.A != 0.0;
         }
-        g.a16.n = n;
-        g.a16.blk_start[n] = t16;
-        g.a16.total_blocks = t16;
-        g.am.n = nm;
-        g.am.blk_start[nm] = tm;
-        g.am.total_blocks = tm;
-        g.blocks16 = t16;
-        g.blocksm = tm;
-        bool st = false;
-        for (int i = 0; i < n; ++i) st = st || hs[i]->d.A != 0.0;
         fs_launcher(h0->d.storage, h0->host.full_tensor != 0, st)(g, h0->stream);
     } else {
+        BatchArgs a;
+        a.n = a.total_blocks = 0;
+        // every lattice's range starts on a whole XCD row group (row_group_remap)
+        for (int i = 0; i < n; ++i)
+            add_lattice(a, hs[i], (hs[i]->nblocks + XCD_GROUP - 1) / XCD_GROUP * XCD_GROUP, flags[i], nuc[i]);
         const int cache = cache_policy(hs, n);
-        if (h0->d.physics == LBM_IMMISCIBLE)
-            colour_launcher(h0->d.storage, cache)(a, total, h0->stream);
+        if (h0->d.physics == LBM_IMMISCIBLE) colour_launcher(h0->d.storage, cache)(a, a.total_blocks, h0->stream);
         step_launcher(h0->d.physics, h0->d.storage, h0->host.full_tensor != 0, h0->host.ms != nullptr, cache)(
-            a, total, h0->stream);
+            a, a.total_blocks, h0->stream);
     }
     if (ndiag) launch_diag(dhs, ndiag, h0->stream);
     const hipError_t e = hipGetLastError();
@@ -1091,10 +1064,8 @@ lbm_status lbm_solute_totals(lbm_t h, double *totals)
         hipLaunchKernelGGL(k_solute_partials<float>, dim3(h->nblocks), dim3(BLOCK), 0, h->stream, (const LatDev *)h->dev, nsp);
     if (const int nc = diag_chunks(h->nblocks)) {
         BatchArgs a;
-        memset(&a, 0, sizeof(a));
-        a.n = 1;
-        a.lat[0] = h->dev;
-        a.blk_start[1] = nc;
+        a.n = a.total_blocks = 0;
+        add_lattice(a, h, nc);
         hipLaunchKernelGGL(k_diag_part, dim3(nc), dim3(BLOCK), 0, h->stream, a);
     }
     hipLaunchKernelGGL(k_solute_final, dim3(1), dim3(BLOCK), 0, h->stream, (const LatDev *)h->dev, nsp);
