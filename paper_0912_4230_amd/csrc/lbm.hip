@@ -264,13 +264,25 @@ using Launch = void (*)(const BatchArgs &, int blocks, hipStream_t);
 // residency at 4 blocks of 256 threads per CU, i.e. 4 waves per SIMD.  Step
 // kernels that fit in fewer than 103 VGPRs would otherwise run 5 waves per
 // SIMD, which measured 2-3% slower on the FP32 miscible and two-fluid steps.
+// So do the FP32 single-fluid (256^3 424 -> 476 us without the reserve).  The
+// 16-bit single-fluid and two-fluid steps are bound by issue and latency, not by
+// the number of streams in flight, and take the waves that fit (62 to 85 VGPRs):
+// channel 160^3 BF16 66.5 -> 61.3 us, 200^3 FP16 split 144 -> 139, 256^3 BF16 split
+// 296 -> 271 (BF16 the same, FP16 231 -> 234), two-fluid 128^3 BF16 77 -> 74,
+// 256^3 545 -> 528, 157^3 FP16 split 166 -> 164.
 constexpr size_t STEP_LDS_RESERVE = 33 * 1024;
+
+template <int P, class S, bool FT, bool MS>
+constexpr size_t step_lds()
+{
+    const bool free = StepWaves<P, S, FT, MS>::value == 5 || (P != PH_MISCIBLE && sizeof(S) == 2);
+    return free ? 0 : STEP_LDS_RESERVE;
+}
 
 template <int P, class S, bool FT, bool MS, int CP>
 void launch_step(const BatchArgs &a, int blocks, hipStream_t s)
 {
-    const size_t lds = StepWaves<P, S, FT, MS>::value == 5 ? 0 : STEP_LDS_RESERVE;
-    hipLaunchKernelGGL((k_step<P, S, FT, MS, CP>), dim3(blocks), dim3(BLOCK), lds, s, a);
+    hipLaunchKernelGGL((k_step<P, S, FT, MS, CP>), dim3(blocks), dim3(BLOCK), (step_lds<P, S, FT, MS>()), s, a);
 }
 
 template <class S, int CP>
