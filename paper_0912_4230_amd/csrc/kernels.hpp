@@ -112,8 +112,8 @@ __device__ inline const GL MsDev *ms_of(const LatDev *L)
 // field was five), and the free-surface block is named here too, so that its
 // fields are fetched with the parameter block's and not after them.  us per step,
 // a table per field against this: 32^3 FP64 channel 6.05 -> 5.7, 48^3 miscible
-// FP32 9.9 -> 9.6, 140 x 140 x 1 free surface 31.9 -> 30.6, 64^3 penetration
-// 23.9 -> 22.8, 256^3 penetration 268 -> 265.
+// FP32 9.9 -> 9.6, 140 x 140 x 1 free surface 31.9 -> 30.7, 64^3 penetration
+// 23.9 -> 22.9.
 struct BatchEntry {
     const LatDev *lat;
     const void *fs;

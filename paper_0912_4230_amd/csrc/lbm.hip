@@ -376,7 +376,7 @@ void launch_fs(const FsGrids &g, hipStream_t s)
     hipLaunchKernelGGL(k_fs_mark, dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
     hipLaunchKernelGGL((k_fs_convert<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
     hipLaunchKernelGGL((k_fs_final<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
-    if (g.am.n) hipLaunchKernelGGL((k_fs_moments<S>), dim3(g.am.n), dim3(BLOCK), 0, s, g.am);
+    if (g.am.n) hipLaunchKernelGGL((k_fs_moments<S>), dim3(g.am.total_blocks), dim3(BLOCK), 0, s, g.am);
 }
 
 using FsLaunch = void (*)(const FsGrids &, hipStream_t);
