@@ -17,6 +17,7 @@
 //                    its receivers
 //   k_fs_final       new classes, masses and fill fractions
 //   k_fs_moments     moments and FP64 diagnostics (moment steps only)
+// Small lattices take the three class passes in one launch (k_fs_classes).
 // Liquid cells cost one byte read and one byte written more than the
 // single-fluid step; gas cells are skipped (waves made only of gas cells
 // store nothing); the class passes read byte planes, 16 cells per thread, of
@@ -631,6 +632,50 @@ __global__ __launch_bounds__(BLOCK) void k_fs_mark(const BatchArgs a)
 // does a cell with these bytes convert (fill, or empty after all)?
 __device__ inline bool converts(int w1, int w2) { return w1 == FS_FILL || empties(w1, w2); }
 
+// A born cell: the equilibrium of the mean density and velocity of its interface
+// neighbours that do not empty (stays(link)), whose rho and V' pass 1 stored (a
+// gas cell has no liquid neighbour), with m = 0.
+template <class S, class Stays>
+__device__ inline void fs_born(const LatDev *L, const GL FsDev *F, int dst, uint32_t idx, const Nbr &b, Stays &&stays)
+{
+    using R = typename Codec<S>::R;
+    [[maybe_unused]] constexpr bool HW = HwMath<S>::value;
+    double rs = 0.0, us[3] = {0.0, 0.0, 0.0};
+    int n = 0;
+    for_groups([&](auto gc) {
+        constexpr int Q0 = decltype(gc)::value;
+        double v[FS_GROUP][4];
+        for_range<Q0, Q0 + FS_GROUP>([&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            const uint32_t j = shifted<Q, 1>(b);
+            if (stays(qc)) {
+                v[Q - Q0][0] = ldg<double>(F->rho, j);
+                for (int k = 0; k < 3; ++k) v[Q - Q0][1 + k] = ldp<double>(F->u, uint32_t(L->ncell), k, j);
+            }
+        });
+        for_range<Q0, Q0 + FS_GROUP>([&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            if (stays(qc)) {
+                rs += v[Q - Q0][0];
+                for (int k = 0; k < 3; ++k) us[k] += v[Q - Q0][1 + k];
+                ++n;
+            }
+        });
+    });
+    // n >= 1: the filling neighbour qualifies
+    const double in = n ? 1.0 / n : 0.0;
+    const double ra = n ? rs * in : 1.0;
+    const double ua[3] = {us[0] * in, us[1] * in, us[2] * in};
+    const R eps = L->uniform_eps ? R(L->eps_u) : ldg<R>(L->eps, idx);
+    const R ur[3] = {R(ua[0]), R(ua[1]), R(ua[2])};
+    R e[NQ];
+    equilibrium<R>(R(ra), ur, rcp<HW>(eps), e);
+    store_all<S>(L->f[dst], L->fm[dst], L->pstride, idx, e);
+    stg<double>(F->mass, idx, 0.0);
+    stg<double>(F->rho, idx, ra);
+    for (int k = 0; k < 3; ++k) stp<double>(F->u, uint32_t(L->ncell), k, idx, ua[k]);
+}
+
 // Pass 3.  Every FS_BORN cell takes the equilibrium of the mean density and
 // velocity of its interface neighbours that do not empty (rho and V' of the
 // step), with m = 0.  Excess mass of each converted cell (m - rho when it
@@ -641,8 +686,6 @@ __device__ inline bool converts(int w1, int w2) { return w1 == FS_FILL || emptie
 template <class S>
 __global__ __launch_bounds__(BLOCK) void k_fs_convert(const BatchArgs a)
 {
-    using R = typename Codec<S>::R;
-    [[maybe_unused]] constexpr bool HW = HwMath<S>::value;
     const FsTile t = fs_tile(a);
     const LatDev *__restrict__ L = t.L;
     const GL FsDev *__restrict__ F = t.F;
@@ -684,42 +727,11 @@ __global__ __launch_bounds__(BLOCK) void k_fs_convert(const BatchArgs a)
                 if (recv & bit(Q)) mark(F, shifted<Q, 1>(b), (uint8_t)(m2[Q] | FS_RECV));
             });
         } else {
-            // born: a gas cell has no liquid neighbour, so the qualifying
-            // neighbours are interface cells, whose rho and V' pass 1 stored
-            double rs = 0.0, us[3] = {0.0, 0.0, 0.0};
-            int n = 0;
-            for_groups([&](auto gc) {
-                constexpr int Q0 = decltype(gc)::value;
-                double v[FS_GROUP][4];
-                for_range<Q0, Q0 + FS_GROUP>([&](auto qc) {
-                    constexpr int Q = decltype(qc)::value;
-                    const uint32_t j = shifted<Q, 1>(b);
-                    if (c[Q] == FS_IF && !empties(f[Q], m2[Q])) {
-                        v[Q - Q0][0] = ldg<double>(F->rho, j);
-                        for (int k = 0; k < 3; ++k) v[Q - Q0][1 + k] = ldp<double>(F->u, t.ncell, k, j);
-                    }
-                });
-                for_range<Q0, Q0 + FS_GROUP>([&](auto qc) {
-                    constexpr int Q = decltype(qc)::value;
-                    if (c[Q] == FS_IF && !empties(f[Q], m2[Q])) {
-                        rs += v[Q - Q0][0];
-                        for (int k = 0; k < 3; ++k) us[k] += v[Q - Q0][1 + k];
-                        ++n;
-                    }
-                });
+            // an interface neighbour's mark byte keeps its other bits in this pass
+            fs_born<S>(t.L, F, dst, idx, b, [&](auto qc) {
+                constexpr int Q = decltype(qc)::value;
+                return c[Q] == FS_IF && !empties(f[Q], m2[Q]);
             });
-            // n >= 1: the filling neighbour qualifies
-            const double in = n ? 1.0 / n : 0.0;
-            const double ra = n ? rs * in : 1.0;
-            const double ua[3] = {us[0] * in, us[1] * in, us[2] * in};
-            const R eps = L->uniform_eps ? R(L->eps_u) : ldg<R>(L->eps, idx);
-            const R ur[3] = {R(ua[0]), R(ua[1]), R(ua[2])};
-            R e[NQ];
-            equilibrium<R>(R(ra), ur, rcp<HW>(eps), e);
-            store_all<S>(L->f[dst], L->fm[dst], L->pstride, idx, e);
-            stg<double>(F->mass, idx, 0.0);
-            stg<double>(F->rho, idx, ra);
-            for (int k = 0; k < 3; ++k) stp<double>(F->u, t.ncell, k, idx, ua[k]);
         }
     });
 }
@@ -835,6 +847,233 @@ __global__ __launch_bounds__(BLOCK) void k_fs_final(const BatchArgs a)
             stg<uint8_t>(F->rowlive[dst], row, ldg<uint8_t>(F->rowlive[dst ^ 1], row));
         }
     }
+}
+
+// The three class passes of a small lattice in one launch, one block: the class
+// and flag of every cell in one byte of LDS (bits 0-1 the class, 2-3 the flag),
+// the marks in its upper bits, a barrier between the passes.  The passes only
+// wait for their dependent loads, which LDS answers within 0.1 us; what is left
+// in memory are the doubles of the cells that convert.  The mark bytes in
+// memory (w2) stay zero.  us per step, three launches / one: 140 x 140 x 1 drop
+// FP64 30.5 / 25.0 (the passes 21 / 13), 239 x 239 x 1 FP32 28.7 / 24.8, 24^3
+// penetration FP64 21.7 / 19.2, 32^3 FP32 20.9 / 19.6, 38^3 BF16 20.7 / 20.6, 100
+// x 10 x 50 FP32 22.6 / 24.4: the converting cells of a large front keep one CU
+// longer than the launches take, so the line lies at 36 K cells, and at what
+// LDS holds for lattices one cell thick, whose front is a line.  (Scanning the
+// cells byte by byte, or working each off on the lane that found it, took 32
+// and 26 us for the drop, 32 and 42 for the 32^3 box.)
+constexpr int FS_SMALL_BLOCK = 1024;
+constexpr uint32_t FS_SMALL_CELLS = 56 * 1024;   // with the list 62 KB of LDS
+constexpr uint32_t FS_SMALL_CELLS_3D = 36 * 1024;
+__host__ __device__ inline bool fs_small(int nx, int ny, int nz)
+{
+    const uint64_t n = uint64_t(nx) * ny * nz;
+    return n <= (nx == 1 || ny == 1 || nz == 1 ? FS_SMALL_CELLS : FS_SMALL_CELLS_3D);
+}
+enum { FSB_FLAG = 0x0c, FSB_BORN = 0x10, FSB_KEEP = 0x20, FSB_TO_IF = 0x40, FSB_RECV = 0x80 };
+
+__device__ inline int fsb_class(int b) { return b & 3; }
+__device__ inline int fsb_flag(int b) { return (b >> 2) & 3; }
+__device__ inline bool fsb_converts(int b)
+{
+    return fsb_flag(b) == FS_FILL || (fsb_flag(b) == FS_EMPTY && !(b & FSB_KEEP));
+}
+
+// Bits 0..15: the bytes of v that have one of `bits`.
+__device__ inline uint32_t bytes_with(const u32x4 &v, uint32_t bits)
+{
+    uint32_t m = 0;
+    if (((v.x | v.y | v.z | v.w) & bits * 0x01010101u) != 0u)
+        for (int k = 0; k < FS_CPT; ++k) m |= (uint32_t(byte_of(v, k)) & bits) != 0u ? 1u << k : 0u;
+    return m;
+}
+
+// work(cell, byte) for every cell whose byte has one of `bits` (cells beyond the
+// last have none), dealt to the threads of the block through a list, however
+// the front lies in the lattice; a list that is full is worked off before the
+// rest is listed.  A thread looks at 16 cells with one load, four times.
+constexpr uint32_t FS_SMALL_LIST = 3 * 1024;
+template <class Work>
+__device__ inline void for_cells(const u32x4 *words, uint32_t ncell, uint32_t bits, uint16_t *list, uint32_t *count,
+                                 Work &&work)
+{
+    static_assert(FS_SMALL_CELLS <= 4 * FS_SMALL_BLOCK * FS_CPT, "one bit for every cell of a thread");
+    uint64_t mine = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t w = k * FS_SMALL_BLOCK + threadIdx.x;
+        if (w * FS_CPT < ncell) mine |= uint64_t(bytes_with(words[w], bits)) << (FS_CPT * k);
+    }
+    bool more;
+    do {
+        if (threadIdx.x == 0) *count = 0;
+        __syncthreads();
+        while (mine) {
+            const uint32_t at = atomicAdd(count, 1u);
+            if (at >= FS_SMALL_LIST) break;
+            const uint32_t bit = uint32_t(__builtin_ctzll(mine));
+            list[at] = uint16_t(((bit / FS_CPT) * FS_SMALL_BLOCK + threadIdx.x) * FS_CPT + bit % FS_CPT);
+            mine &= mine - 1;
+        }
+        __syncthreads();
+        const uint32_t n = min(*count, FS_SMALL_LIST);
+        for (uint32_t i = threadIdx.x; i < n; i += FS_SMALL_BLOCK) {
+            const uint32_t idx = list[i];
+            work(idx, int(reinterpret_cast<const unsigned char *>(words)[idx]));
+        }
+        more = __syncthreads_or(mine != 0) != 0;
+    } while (more);
+}
+
+template <class S>
+__global__ __launch_bounds__(FS_SMALL_BLOCK) void k_fs_classes(const BatchArgs a)
+{
+    using R = typename Codec<S>::R;
+    __shared__ u32x4 words[FS_SMALL_CELLS / FS_CPT];
+    __shared__ uint32_t count;
+    __shared__ uint16_t list[FS_SMALL_LIST];
+    const unsigned char *B = reinterpret_cast<const unsigned char *>(words);
+    const LatDev *__restrict__ L = a.e[blockIdx.x].lat;
+    const GL FsDev *__restrict__ F = fs_block(a.e[blockIdx.x].fs);
+    const int src = a.e[blockIdx.x].flags & 1, dst = src ^ 1;
+    const uint32_t ncell = L->ncell, nrow = (ncell + BLOCK - 1) / BLOCK;
+    const auto mark_byte = [&](uint32_t j, uint32_t v) {
+        atomicOr(reinterpret_cast<uint32_t *>(words) + j / 4, v << (8 * (j & 3)));
+    };
+    const auto around = [&](const Nbr &b, int *v) {
+        for_links([&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            v[Q] = B[shifted<Q, 1>(b)];
+        });
+    };
+
+    for (uint32_t w = threadIdx.x; w * FS_CPT < ncell; w += FS_SMALL_BLOCK) {
+        const u32x4 c = ld16(F->cls, w * FS_CPT), f = ld16(F->w1, w * FS_CPT);
+        u32x4 v = c | f << 2;
+        // no bits for what lies beyond the last cell
+        const uint32_t left = ncell - w * FS_CPT;
+        if (left < FS_CPT) {
+            for (uint32_t k = 0; k < 4; ++k)
+                v[k] = left <= 4 * k ? 0u : (left < 4 * k + 4 ? v[k] & ((1u << (8 * (left - 4 * k))) - 1u) : v[k]);
+        }
+        words[w] = v;
+    }
+    // the launch-order list pass 1 has just used serves the next step again:
+    // unlist its rows
+    const uint32_t listed = min(ldg<uint32_t>(F->hcount[src], 0), nrow);
+    for (uint32_t i = threadIdx.x; i < listed; i += FS_SMALL_BLOCK) {
+        const uint32_t r = ldg<uint32_t>(F->hlist[src], i);
+        if (r < nrow) stg<uint32_t>(F->hpos[src], r, 0u);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) stg<uint32_t>(F->hcount[src], 0, 0u);
+
+    // pass 2
+    for_cells(words, ncell, FSB_FLAG, list, &count, [&](uint32_t idx, int own) {
+        const Nbr b = nbr_of(L, idx);
+        int v[NQ];
+        around(b, v);
+        const bool fills = fsb_flag(own) == FS_FILL;
+        bool near_fill = false;
+        for_links([&](auto qc) { near_fill = near_fill || fsb_flag(v[decltype(qc)::value]) == FS_FILL; });
+        if (!fills && near_fill) {
+            mark_byte(idx, FSB_KEEP);
+            return;
+        }
+        for_links([&](auto qc) {
+            constexpr int Q = decltype(qc)::value;
+            if (fsb_class(v[Q]) == (fills ? FS_GAS : FS_LIQ)) mark_byte(shifted<Q, 1>(b), fills ? FSB_BORN : FSB_TO_IF);
+        });
+    });
+
+    // pass 3
+    for_cells(words, ncell, FSB_FLAG | FSB_BORN, list, &count, [&](uint32_t idx, int own) {
+        const bool conv = fsb_converts(own);
+        if (!conv && !(own & FSB_BORN)) return;   // kept
+        const Nbr b = nbr_of(L, idx);
+        int v[NQ];
+        around(b, v);
+        if (conv) {
+            const double m = ldg<double>(F->mass, idx), rho = ldg<double>(F->rho, idx);
+            int n = 0;
+            for_links([&](auto qc) {
+                constexpr int Q = decltype(qc)::value;
+                if ((fsb_class(v[Q]) == FS_IF && !fsb_converts(v[Q])) || (v[Q] & (FSB_BORN | FSB_TO_IF))) {
+                    ++n;
+                    mark_byte(shifted<Q, 1>(b), FSB_RECV);
+                }
+            });
+            const double ex = fsb_flag(own) == FS_FILL ? m - rho : m;
+            stg<double>(F->share, idx, n ? ex / n : 0.0);
+            if (!n) atomicAdd(F->lost, ex);
+        } else {
+            fs_born<S>(L, F, dst, idx, b, [&](auto qc) {
+                const int w = v[decltype(qc)::value];
+                return fsb_class(w) == FS_IF && !(fsb_converts(w) && fsb_flag(w) == FS_EMPTY);
+            });
+        }
+    });
+
+    // pass 4; a row keeps its place in the next pass 1 as in k_fs_final
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t w = k * FS_SMALL_BLOCK + threadIdx.x;
+        bool keep = false;
+        if (w * FS_CPT < ncell) {
+            const u32x4 v = words[w];
+            // interface and liquid cells have exactly one class bit
+            const uint32_t one = (v.x ^ v.x >> 1) | (v.y ^ v.y >> 1) | (v.z ^ v.z >> 1) | (v.w ^ v.w >> 1);
+            keep = (one & 0x01010101u) != 0u || ((v.x | v.y | v.z | v.w) & (FSB_FLAG | FSB_BORN) * 0x01010101u) != 0u;
+        }
+        constexpr int TPR = BLOCK / FS_CPT;
+        const uint64_t vote = __builtin_amdgcn_ballot_w64(keep);
+        const int lane = threadIdx.x & 63;
+        if (lane % TPR == 0 && w * FS_CPT < ncell) {
+            const uint32_t row = w / TPR;
+            stg<uint8_t>(F->rowlive[dst], row, ((vote >> lane) & ((uint64_t(1) << TPR) - 1)) != 0 ? 1 : 0);
+            stg<uint8_t>(F->rowwork, row, 0);
+        }
+    }
+    for_cells(words, ncell, FSB_FLAG | FSB_BORN | FSB_TO_IF | FSB_RECV, list, &count, [&](uint32_t idx, int own) {
+        if (fsb_converts(own)) {
+            stg<uint8_t>(F->cls, idx, fsb_flag(own) == FS_FILL ? FS_LIQ : FS_GAS);
+            return;
+        }
+        if (!(own & (FSB_BORN | FSB_TO_IF | FSB_RECV))) return;   // kept, no share
+        double m, r;
+        if (own & FSB_TO_IF) {          // a liquid cell: m = its density
+            R o[NQ];
+            load_cell<S>(L->f[dst], L->fm[dst], L->pstride, idx, o);
+            R dr = 0;
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) dr += o[q];
+            r = 1.0 + double(dr);
+            m = r;
+        } else {
+            r = ldg<double>(F->rho, idx);
+            m = own & FSB_BORN ? 0.0 : ldg<double>(F->mass, idx);
+        }
+        if (own & FSB_RECV) {
+            const Nbr b = nbr_of(L, idx);
+            int v[NQ];
+            double sh[NQ];
+            around(b, v);
+            for_links([&](auto qc) {
+                constexpr int Q = decltype(qc)::value;
+                sh[Q] = ldg<double>(F->share, fsb_converts(v[Q]) ? shifted<Q, 1>(b) : idx);
+            });
+            for_links([&](auto qc) {
+                constexpr int Q = decltype(qc)::value;
+                if (fsb_converts(v[Q])) m += sh[Q];
+            });
+        }
+        stg<double>(F->mass, idx, m);
+        stg<double>(F->lam[dst], idx, m / r);
+        if (own & (FSB_BORN | FSB_TO_IF)) {
+            stg<uint8_t>(F->cls, idx, FS_IF);
+            fs_list_row(F, dst, idx / BLOCK, nrow);
+        }
+    });
 }
 
 // Moment steps, after pass 4 (one thread per cell, the step grid): rho, V'

@@ -362,7 +362,7 @@ Launch colour_launcher(int storage, int cache)
 int fs_prefix_blocks(int rows) { return std::min(rows, std::max(64, rows / 32)); }
 
 struct FsGrids {
-    BatchArgs a, a16, am;
+    BatchArgs a, a16, as, am;
 };
 
 #ifndef PLBM_FS_LDS
@@ -373,9 +373,12 @@ template <class S, bool FT, bool ST>
 void launch_fs(const FsGrids &g, hipStream_t s)
 {
     hipLaunchKernelGGL((k_fs_step<S, FT, ST>), dim3(g.a.total_blocks), dim3(BLOCK), PLBM_FS_LDS, s, g.a);
-    hipLaunchKernelGGL(k_fs_mark, dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
-    hipLaunchKernelGGL((k_fs_convert<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
-    hipLaunchKernelGGL((k_fs_final<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
+    if (g.a16.n) {
+        hipLaunchKernelGGL(k_fs_mark, dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
+        hipLaunchKernelGGL((k_fs_convert<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
+        hipLaunchKernelGGL((k_fs_final<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
+    }
+    if (g.as.n) hipLaunchKernelGGL((k_fs_classes<S>), dim3(g.as.n), dim3(FS_SMALL_BLOCK), 0, s, g.as);
     if (g.am.n) hipLaunchKernelGGL((k_fs_moments<S>), dim3(g.am.total_blocks), dim3(BLOCK), 0, s, g.am);
 }
 
@@ -573,12 +576,13 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
         // pass 1: per lattice a prefix of blocks for the rows listed as
         // holding interface cells, then one block per row
         FsGrids g;
-        g.a.n = g.a.total_blocks = g.a16.n = g.a16.total_blocks = g.am.n = g.am.total_blocks = 0;
+        for (BatchArgs *p : {&g.a, &g.a16, &g.as, &g.am}) p->n = p->total_blocks = 0;
         bool st = false;
         for (int i = 0; i < n; ++i) {
             const lbm_sim *h = hs[i];
             add_lattice(g.a, h, fs_prefix_blocks(h->nblocks) + h->nblocks, flags[i], nuc[i]);
-            add_lattice(g.a16, h, (h->host.ncell + BLOCK * FS_CPT - 1) / (BLOCK * FS_CPT), flags[i]);
+            if (fs_small(h->d.nx, h->d.ny, h->d.nz)) add_lattice(g.as, h, 1, flags[i]);
+            else add_lattice(g.a16, h, (h->host.ncell + BLOCK * FS_CPT - 1) / (BLOCK * FS_CPT), flags[i]);
             if (flags[i] & 2) add_lattice(g.am, h, h->nblocks, flags[i]);
             st = st || h->d.A != 0.0;
         }
