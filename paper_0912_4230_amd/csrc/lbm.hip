@@ -496,9 +496,13 @@ bool diag_step(const lbm_sim *h, long long t, bool last)
 // 122 / 128); bounced links read a line once more (10% obstacles 256^3 1120 /
 // 1035, BF16 567 / 553).  The paired 16-bit planes of the miscible model gain
 // only where rows are not whole sectors of 32 bytes (tensor 243 x 251 x 238 BF16
-// 560 / 544; 200^3 BF16 254 / 255), the split forms hardly (590 / 583; 211 x 190
-// x 177 BF16 split 271 / 274).  The FP32 tensor step
-// gains with whole lines too (256^3 1029 / 1008; BF16 590 / 600).
+// 562 / 546; 200^3 BF16 254 / 255), the split forms among them only in larger
+// lattices (251^3 BF16 split 621 / 608, 101 x 310 x 299 FP16 split 372 / 365, 200^3
+// with 10% obstacles 364 / 354, but 155 x 151 x 140 136.8 / 139.0: the line lies
+// between, at 6M cells).  The FP32 tensor step gains with whole lines too where
+// it is larger still (224^3 719 / 698, 256^3 1050 / 1025, 320 x 256 x 256 1343 /
+// 1302, but 128 x 256 x 300 603 / 611, 192^3 417 / 439, 128^3 125 / 136: 10.5M
+// cells).
 //
 // The lattices of a batch share the launch: their bytes add up, and the larger
 // part of their cells decides between REUSE and STREAM.
@@ -515,9 +519,10 @@ int cache_policy(lbm_sim *const *hs, int n)
         bytes += double(hs[i]->lay.total - hs[i]->lay.f0);
         cells += hs[i]->host.ncell;
         const bool shared = row % (paired ? 32 : 128) != 0 || hs[i]->host.links;
-        if (paired ? shared && !split_storage(d->storage)
-                   : shared || (hs[i]->host.full_tensor && d->storage == LBM_F32))
-            reuse += hs[i]->host.ncell;
+        const double own = hs[i]->host.ncell;
+        if (paired ? shared && (!split_storage(d->storage) || own > 6e6)
+                   : shared || (hs[i]->host.full_tensor && d->storage == LBM_F32 && own > 10.5e6))
+            reuse += own;
     }
     const lbm_desc *d0 = &hs[0]->d;
     const bool wide = d0->physics == LBM_MISCIBLE && !paired_storage(d0);
