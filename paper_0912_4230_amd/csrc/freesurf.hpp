@@ -233,7 +233,7 @@ template <> struct FsWaves<float, false, false> { static constexpr int value = 7
 // processed exactly once, and no cell reads what another writes in this pass,
 // so the order changes no result.
 
-template <class S, bool FT, bool ST = false>
+template <class S, bool FT, bool ST = false, int CP = CACHE_STREAM>
 __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>::value))) void k_fs_step(const BatchArgs a)
 {
     using R = typename Codec<S>::R;
@@ -284,7 +284,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>:
         b.bb = live ? b.bb : 0u;
         // split codecs: the 19 mass loads (sharing the x-links' masses across
         // the wave measured 4% slower here in BF16, which spills at 7 waves)
-        pull_all<S, false>(L->f[src], L->fm[src], L->pstride, cell, b, d);
+        pull_all<S, false, CP == CACHE_STREAM>(L->f[src], L->fm[src], L->pstride, cell, b, d);
         const R eps = L->uniform_eps ? R(L->eps_u) : ldg<R>(L->eps, cell);
         const R ie = rcp<HW>(eps);
         double m = 0.0;
@@ -431,7 +431,7 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>:
         stg<uint8_t>(F->rowwork, row, 1);
     // waves made only of gas and solid cells store nothing
     if (idx < ncell && any_live)
-        store_all<S>(L->f[dst], L->fm[dst], L->pstride, idx, d);
+        store_all<S, CP == CACHE_KEEP>(L->f[dst], L->fm[dst], L->pstride, idx, d);
     if (__builtin_amdgcn_ballot_w64(cls == FS_IF) != 0 && (threadIdx.x & 63) == 0) fs_list_row(F, dst, row, nrow);
 }
 

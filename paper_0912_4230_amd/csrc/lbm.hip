@@ -369,10 +369,10 @@ struct FsGrids {
 #define PLBM_FS_LDS 0
 #endif
 
-template <class S, bool FT, bool ST>
+template <class S, bool FT, bool ST, int CP>
 void launch_fs(const FsGrids &g, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_fs_step<S, FT, ST>), dim3(g.a.total_blocks), dim3(BLOCK), PLBM_FS_LDS, s, g.a);
+    hipLaunchKernelGGL((k_fs_step<S, FT, ST, CP>), dim3(g.a.total_blocks), dim3(BLOCK), PLBM_FS_LDS, s, g.a);
     if (g.a16.n) {
         hipLaunchKernelGGL(k_fs_mark, dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
         hipLaunchKernelGGL((k_fs_convert<S>), dim3(g.a16.total_blocks), dim3(BLOCK), 0, s, g.a16);
@@ -384,25 +384,32 @@ void launch_fs(const FsGrids &g, hipStream_t s)
 
 using FsLaunch = void (*)(const FsGrids &, hipStream_t);
 
-template <bool FT, bool ST>
+template <bool FT, bool ST, int CP>
 FsLaunch fs_for_storage(int storage)
 {
     switch (storage) {
-    case LBM_F64: return launch_fs<double, FT, ST>;
-    case LBM_F32: return launch_fs<float, FT, ST>;
-    case LBM_BF16_DEV: return launch_fs<bf16_t, FT, ST>;
-    case LBM_F16_DEV: return launch_fs<f16_t, FT, ST>;
-    case LBM_BF16_SPLIT: return launch_fs<bf16s_t, FT, ST>;
-    default: return launch_fs<f16s_t, FT, ST>;
+    case LBM_F64: return launch_fs<double, FT, ST, CP>;
+    case LBM_F32: return launch_fs<float, FT, ST, CP>;
+    case LBM_BF16_DEV: return launch_fs<bf16_t, FT, ST, CP>;
+    case LBM_F16_DEV: return launch_fs<f16_t, FT, ST, CP>;
+    case LBM_BF16_SPLIT: return launch_fs<bf16s_t, FT, ST, CP>;
+    default: return launch_fs<f16s_t, FT, ST, CP>;
     }
 }
 
 // the surface-tension form when any lattice of the batch has A != 0 (with
 // A = 0 it computes exactly what the plain form does)
-FsLaunch fs_launcher(int storage, bool full_tensor, bool st)
+template <int CP>
+FsLaunch fs_for_cache(int storage, bool full_tensor, bool st)
 {
-    if (st) return full_tensor ? fs_for_storage<true, true>(storage) : fs_for_storage<false, true>(storage);
-    return full_tensor ? fs_for_storage<true, false>(storage) : fs_for_storage<false, false>(storage);
+    if (st) return full_tensor ? fs_for_storage<true, true, CP>(storage) : fs_for_storage<false, true, CP>(storage);
+    return full_tensor ? fs_for_storage<true, false, CP>(storage) : fs_for_storage<false, false, CP>(storage);
+}
+
+FsLaunch fs_launcher(int storage, bool full_tensor, bool st, int cache)
+{
+    return cache == CACHE_KEEP ? fs_for_cache<CACHE_KEEP>(storage, full_tensor, st)
+                               : fs_for_cache<CACHE_STREAM>(storage, full_tensor, st);
 }
 
 template <int P, class S>
@@ -504,6 +511,13 @@ bool diag_step(const lbm_sim *h, long long t, bool last)
 // 1302, but 128 x 256 x 300 603 / 611, 192^3 417 / 439, 128^3 125 / 136: 10.5M
 // cells).
 //
+// The free-surface step leaves the gas cells out; KEEP from 50 to 256 MB of
+// populations there, STREAM else (us, whole step, STREAM / KEEP: 48^3 FP32 17 MB
+// 24.8 / 25.2, 61 x 71 x 81 53 MB 30.0 / 29.4, 101 x 100 x 97 149 MB 34.8 / 32.9,
+// FP16 split 82 MB 33.2 / 31.1, 110^3 202 MB 36.4 / 34.3, 128^3 BF16 159 MB 33.6 /
+// 33.8; 128^3 319 MB 44.5 / 45.2, 200 x 190 x 180 1040 MB 130 / 139); plain loads
+// alone gain nothing.
+//
 // The lattices of a batch share the launch: their bytes add up, and the larger
 // part of their cells decides between REUSE and STREAM.
 int cache_policy(lbm_sim *const *hs, int n)
@@ -516,7 +530,7 @@ int cache_policy(lbm_sim *const *hs, int n)
         const bool paired = paired_storage(d);
         const size_t row = (size_t)d->nx * storage_bytes(d->storage) * (paired ? 2 : 1);
         whole_lines = whole_lines && row % 128 == 0;
-        bytes += double(hs[i]->lay.total - hs[i]->lay.f0);
+        bytes += double((d->physics == LBM_FREESURF ? hs[i]->lay.fs : hs[i]->lay.total) - hs[i]->lay.f0);
         cells += hs[i]->host.ncell;
         const bool shared = row % (paired ? 32 : 128) != 0 || hs[i]->host.links;
         const double own = hs[i]->host.ncell;
@@ -527,6 +541,7 @@ int cache_policy(lbm_sim *const *hs, int n)
     const lbm_desc *d0 = &hs[0]->d;
     const bool wide = d0->physics == LBM_MISCIBLE && !paired_storage(d0);
     const double tiny = d0->physics == LBM_SINGLE ? 24 * MB : 12 * MB;
+    if (d0->physics == LBM_FREESURF) return bytes >= 50 * MB && bytes <= 256 * MB ? CACHE_KEEP : CACHE_STREAM;
     const double low = wide ? (whole_lines ? 96 * MB : 62 * MB) : 50 * MB;
     if (bytes <= tiny || (bytes >= low && bytes <= 256 * MB)) return CACHE_KEEP;
     return bytes > low && 2 * reuse > cells ? CACHE_REUSE : CACHE_STREAM;
@@ -591,7 +606,7 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
             if (flags[i] & 2) add_lattice(g.am, h, h->nblocks, flags[i]);
             st = st || h->d.A != 0.0;
         }
-        fs_launcher(h0->d.storage, h0->host.full_tensor != 0, st)(g, h0->stream);
+        fs_launcher(h0->d.storage, h0->host.full_tensor != 0, st, cache_policy(hs, n))(g, h0->stream);
     } else {
         BatchArgs a;
         a.n = a.total_blocks = 0;
