@@ -304,7 +304,7 @@ def fs_bytes_per_live_cell(st):
 def freesurface_leg(n, steps, warmup, storages=("f32", "bf16")):
     """Free surface (Sec. 3).  (a) Liquid penetrating the unsaturated
     spruce-like medium, n^3, liquid in the upper half, gravity along the
-    grain: five launches per step; algorithmic bytes of the step = the
+    grain: four launches per step; algorithmic bytes of the step = the
     stream/collide of the live cells (fs_bytes_per_live_cell) + 2 bytes per
     cell (class read, flag written) + 9 bytes per cell for the class passes.
     (b) The paper's droplet (Sec. 5.3): 140x140x1, R = 8, tau = 0.7, G = 1e-6,

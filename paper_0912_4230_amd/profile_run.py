@@ -5,7 +5,7 @@
 
 `step` sets up one lattice of the chosen workload and runs the given number
 of steps (one step kernel launch each, plus the colour pass in two-fluid
-mode, or the five launches of a free-surface step); `copy` runs torch's
+mode, or the four launches of a free-surface step); `copy` runs torch's
 device-to-device copy of a buffer of known size, the reference kernel used
 to scale the FETCH_SIZE / WRITE_SIZE counters to bytes, or (--kernel f4) the
 float4 non-temporal streaming copy of the probe library, the practical
