@@ -319,7 +319,9 @@ long long lbm_steps_done(lbm_t h);
  * its process, saves and restores them).  A checkpoint is opaque host bytes:
  * a header, then every byte of the lattice's workspace (populations of both
  * copies, masses, medium planes, diagnostics, free-surface state, further
- * solutes) except the blocks that hold device addresses.
+ * solutes) except the blocks that hold device addresses. Padding and planes
+ * that the lattice does not use come as they lie in the workspace, so two
+ * checkpoints of one state can differ there; no call reads those bytes.
  *
  * lbm_state_bytes: the size of a checkpoint of h (about its workspace size),
  * or 0 for a NULL handle.

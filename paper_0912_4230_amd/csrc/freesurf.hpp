@@ -1160,7 +1160,8 @@ __global__ __launch_bounds__(BLOCK) void k_fs_init_state(const LatDev *L, const 
         l = cls == FS_LIQ ? 1.0 : (cls == FS_IF ? fmin(fmax(l, 0.0), 1.0) : 0.0);
         stg<uint8_t>(F->cls, idx, (unsigned char)cls);
         stg<uint8_t>(F->w2, idx, 0);
-        stg<double>(F->lam[0], idx, l);   // pass 1 writes the other copy before it is read
+        stg<double>(F->lam[0], idx, l);
+        stg<double>(F->lam[1], idx, l);   // pass 1 writes interface cells only; a checkpoint holds the plane
         stg<double>(F->mass, idx, l * r0);
         stg<double>(F->rho, idx, cls == FS_IF || cls == FS_LIQ ? r0 : 0.0);
         void *M = L->mom;

@@ -1863,7 +1863,8 @@ __global__ __launch_bounds__(BLOCK) void k_init(const InitArgs<typename Codec<S>
     // not solid (free surface: a cell with liquid), so only the others are set
     // up in both copies (writing all of both was half of this kernel's bytes:
     // 61^3 miscible FP32 17 -> 12 us; 256^3 free surface, half of it gas, 600
-    // -> 475 us).
+    // -> 475 us).  A checkpoint taken before that step holds this copy's bytes
+    // in the other's place (lbm_save_state).
     const bool stepped = type != CELL_SOLID && !(L->physics == PH_FREESURF && !(c0 > R(0)));
     const int ncopy = __builtin_amdgcn_ballot_w64(stepped) != 0 ? 1 : 2;
     for (int cpy = 0; cpy < ncopy; ++cpy) {

@@ -798,6 +798,33 @@ int state_spans(const lbm_sim *h, Span out[3])
     return n;
 }
 
+// Until the first step the other copy of the populations (and masses) is unset
+// wherever that step writes it (k_init): in a checkpoint of a lattice that has
+// not stepped, at `out`, the current copy's bytes take its place.
+void fill_other_copy(const lbm_sim *h, const Span *sp, int n, char *out)
+{
+    const auto at = [&](size_t off) {
+        char *o = out;
+        for (int k = 0; k < n; ++k) {
+            if (off >= sp[k].off && off < sp[k].off + sp[k].len) return o + (off - sp[k].off);
+            o += sp[k].len;
+        }
+        return static_cast<char *>(nullptr);
+    };
+    const auto copy = [&](size_t off0, size_t off1, size_t len) {
+        if (len) memcpy(at(h->cur ? off0 : off1), at(h->cur ? off1 : off0), len);
+    };
+    const Layout &L = h->lay;
+    copy(L.f0, L.f1, L.f1 - L.f0);
+    copy(L.h0, L.h1, L.h1 - L.h0);
+    copy(L.fm0, L.fm1, L.fm1 - L.fm0);
+    copy(L.hm0, L.hm1, L.hm1 - L.hm0);
+    for (int k = 0; k < extra_species(&h->d); ++k) {
+        copy(L.msx[k][0], L.msx[k][1], L.msx[k][1] - L.msx[k][0]);
+        copy(L.msm[k][0], L.msm[k][1], L.msm[k][1] - L.msm[k][0]);
+    }
+}
+
 CkptHeader ckpt_header(const lbm_sim *h)
 {
     CkptHeader H;
@@ -1172,7 +1199,9 @@ lbm_status lbm_save_state(lbm_t h, void *host_dst, size_t bytes)
         if ((st = dev_err(hipMemcpyAsync(o, h->ws + sp[k].off, sp[k].len, hipMemcpyDeviceToHost, h->stream)))) return st;
         o += sp[k].len;
     }
-    return dev_err(hipStreamSynchronize(h->stream));
+    if ((st = dev_err(hipStreamSynchronize(h->stream)))) return st;
+    if (h->steps == 0) fill_other_copy(h, sp, n, static_cast<char *>(host_dst) + sizeof(H));
+    return LBM_OK;
 }
 
 lbm_status lbm_load_state(lbm_t h, const void *host_src, size_t bytes)
