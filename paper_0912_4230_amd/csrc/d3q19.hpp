@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "cache_policy.hpp"
+
 // global (HBM) address space: loads and stores through such pointers compile
 // to global_* instructions instead of flat_*
 #define GL __attribute__((address_space(1)))
@@ -54,17 +56,7 @@ __host__ __device__ constexpr float weight<float>(int q)
 
 // ---------------------------------------------------------------------------
 // storage codecs: Codec<S>::R is the compute type, load/store convert.
-//
-// Cache policy of the populations in a step.  Loads (NT): non-temporal, or plain.
-// Stores (WT): non-temporal, or written through to the memory side at once (a
-// relaxed store of agent scope), which leaves nothing dirty in the L2s for the
-// end of the launch and the values in the memory-side cache (256 MB).  The
-// launch chooses (lbm.hip: cache_policy, where both sides' times stand).
-enum {
-    CACHE_STREAM = 0,   // non-temporal loads and stores
-    CACHE_REUSE = 1,    // plain loads, non-temporal stores
-    CACHE_KEEP = 2      // plain loads, stores written through
-};
+// NT, WT: the cache policy (cache_policy.hpp).
 
 template <bool WT, class T>
 __device__ inline void st(GL T *p, T v)

@@ -23,15 +23,6 @@ constexpr size_t ALIGN = 256;
 
 size_t align_up(size_t v) { return (v + ALIGN - 1) / ALIGN * ALIGN; }
 
-size_t storage_bytes(int storage)
-{
-    switch (storage) {
-    case LBM_F64: return 8;
-    case LBM_F32: return 4;
-    default: return 2;
-    }
-}
-
 size_t real_bytes(int storage) { return storage == LBM_F64 ? 8 : 4; }
 
 // Elements from one population plane to the next.  Every plane starts on a
@@ -63,10 +54,7 @@ size_t plane_stride(const lbm_desc *d)
     return plane_stride_of((size_t)d->nx * d->ny * d->nz, storage_bytes(d->storage));
 }
 
-// Miscible lattices in 16-bit storage keep f and h in paired planes of
-// 32-bit words (and split codecs their two masses as one 8-byte pair per
-// cell); the planes are padded as planes of 4-byte elements.
-bool paired_storage(const lbm_desc *d) { return d->physics == LBM_MISCIBLE && storage_bytes(d->storage) == 2; }
+bool paired_storage(const lbm_desc *d) { return plbm::paired_storage(d->physics, d->storage); }
 
 size_t pair_plane_stride(const lbm_desc *d)
 {
@@ -81,8 +69,6 @@ struct Layout {
 
 // solutes beyond the first
 int extra_species(const lbm_desc *d) { return (d->physics == LBM_MISCIBLE && d->nspecies > 1) ? d->nspecies - 1 : 0; }
-
-bool split_storage(int storage) { return storage == LBM_BF16_SPLIT || storage == LBM_F16_SPLIT; }
 
 // a second lattice (solute or fluid 1)
 bool two_lattices(int physics) { return physics == LBM_MISCIBLE || physics == LBM_IMMISCIBLE; }
@@ -477,74 +463,31 @@ bool diag_step(const lbm_sim *h, long long t, bool last)
     return last || (h->d.diag_every > 0 && t % h->d.diag_every == 0);
 }
 
-// Cache policy of the populations in a step of these lattices (results are
-// bitwise the same under all three).  us per step, FP32 miscible unless named,
-// CACHE_STREAM / CACHE_REUSE / CACHE_KEEP:
-//
-// KEEP, when all the launch's populations (both copies) fit in the memory-side
-// cache (256 MB): a step then reads what the last one left there, where
-// non-temporal stores send it to memory.
-//   61^3 (69 MB) 15.4 / 15.7 / 13.6, 83^3 (174 MB) 40 / 39 / 32.6, 94^3 (252 MB)
-//   57 / 56 / 46, 98^3 (286 MB) 66 / 63 / 67; 70^3 BF16 (52 MB) 15.3 / 16.1 /
-//   14.4, 110^3 BF16 (202 MB) 47 / 46 / 41, 120^3 BF16 (263 MB) 59 / 57 / 60;
-//   two-fluid 80^3 36 / 37 / 30; channel FP64 64^3 17 / 18 / 14.
-// Lattices that the L2s (32 MB) hold in part step as fast or faster under STREAM:
-//   48^3 9.6 / 10.2 / 10.7, 58^3 12.0 / 13.4 / 12.6, 64^3 BF16 9.2 / 10.5 / 10.4;
-// the line lies at 62 MB in the miscible model in FP32 and FP64 (96 MB with rows
-// of whole lines: 64^3, 80 MB, 14.4 / 15.9 / 14.8), at 50 MB else.  The smallest
-// gain again (32^3 FP64 channel, 10 MB, 6.6 / 6.6 / 6.0; 64^3 BF16 channel, 20
-// MB, 8.0 / 7.3 / 7.0; miscible 32^3, 10 MB, 7.9 / 7.9 / 7.7, but 40^3, 20 MB,
-// 8.3 / 8.9 / 9.0).
-//
-// REUSE, when lines are read by two waves: rows that are not whole lines put
-// most lines across a wave boundary (243 x 251 x 238 970 / 935, tensor 1075 /
-// 997; 250^3 988 / 936; 131^3 two-fluid 142 / 135, BF16 93 / 87; channel 150^3
-// FP64 201 / 190; where rows are whole lines 256^3 945 / 970, 128^3 two-fluid
-// 122 / 128); bounced links read a line once more (10% obstacles 256^3 1120 /
-// 1035, BF16 567 / 553).  The paired 16-bit planes of the miscible model gain
-// only where rows are not whole sectors of 32 bytes (tensor 243 x 251 x 238 BF16
-// 562 / 546; 200^3 BF16 254 / 255), the split forms among them only in larger
-// lattices (251^3 BF16 split 621 / 608, 101 x 310 x 299 FP16 split 372 / 365, 200^3
-// with 10% obstacles 364 / 354, but 155 x 151 x 140 136.8 / 139.0: the line lies
-// between, at 6M cells).  The FP32 tensor step gains with whole lines too where
-// it is larger still (224^3 719 / 698, 256^3 1050 / 1025, 320 x 256 x 256 1343 /
-// 1302, but 128 x 256 x 300 603 / 611, 192^3 417 / 439, 128^3 125 / 136: 10.5M
-// cells).
-//
-// The free-surface step leaves the gas cells out; KEEP from 50 to 256 MB of
-// populations there, STREAM else (us, whole step, STREAM / KEEP: 48^3 FP32 17 MB
-// 24.8 / 25.2, 61 x 71 x 81 53 MB 30.0 / 29.4, 101 x 100 x 97 149 MB 34.8 / 32.9,
-// FP16 split 82 MB 33.2 / 31.1, 110^3 202 MB 36.4 / 34.3, 128^3 BF16 159 MB 33.6 /
-// 33.8; 128^3 319 MB 44.5 / 45.2, 200 x 190 x 180 1040 MB 130 / 139); plain loads
-// alone gain nothing.
-//
-// The lattices of a batch share the launch: their bytes add up, and the larger
-// part of their cells decides between REUSE and STREAM.
-int cache_policy(lbm_sim *const *hs, int n)
+CacheLattice cache_lattice(const lbm_sim *h)
 {
-    constexpr double MB = 1e6;
-    double bytes = 0, cells = 0, reuse = 0;
-    bool whole_lines = true;
-    for (int i = 0; i < n; ++i) {
-        const lbm_desc *d = &hs[i]->d;
-        const bool paired = paired_storage(d);
-        const size_t row = (size_t)d->nx * storage_bytes(d->storage) * (paired ? 2 : 1);
-        whole_lines = whole_lines && row % 128 == 0;
-        bytes += double((d->physics == LBM_FREESURF ? hs[i]->lay.fs : hs[i]->lay.total) - hs[i]->lay.f0);
-        cells += hs[i]->host.ncell;
-        const bool shared = row % (paired ? 32 : 128) != 0 || hs[i]->host.links;
-        const double own = hs[i]->host.ncell;
-        if (paired ? shared && (!split_storage(d->storage) || own > 6e6)
-                   : shared || (hs[i]->host.full_tensor && d->storage == LBM_F32 && own > 10.5e6))
-            reuse += own;
-    }
-    const lbm_desc *d0 = &hs[0]->d;
-    const bool wide = d0->physics == LBM_MISCIBLE && !paired_storage(d0);
-    const double tiny = d0->physics == LBM_SINGLE ? 24 * MB : 12 * MB;
-    if (d0->physics == LBM_FREESURF) return bytes >= 50 * MB && bytes <= 256 * MB ? CACHE_KEEP : CACHE_STREAM;
-    const double low = wide ? (whole_lines ? 96 * MB : 62 * MB) : 50 * MB;
-    if (bytes <= tiny || (bytes >= low && bytes <= 256 * MB)) return CACHE_KEEP;
-    return bytes > low && 2 * reuse > cells ? CACHE_REUSE : CACHE_STREAM;
+    const lbm_desc *d = &h->d;
+    CacheLattice c;
+    c.physics = d->physics;
+    c.storage = d->storage;
+    c.nx = d->nx;
+    c.links = h->host.links != nullptr;
+    c.tensor = h->host.full_tensor != 0;
+    c.cells = h->host.ncell;
+    c.bytes = double((d->physics == LBM_FREESURF ? h->lay.fs : h->lay.total) - h->lay.f0);
+    return c;
+}
+
+void cache_lattices(lbm_sim *const *hs, int n, CacheLattice out[MAXB])
+{
+    for (int i = 0; i < n; ++i) out[i] = cache_lattice(hs[i]);
+}
+
+// the bytes a group would keep in the memory-side cache (keep_bytes)
+double group_keep(lbm_sim *const *hs, int n)
+{
+    CacheLattice cl[MAXB];
+    cache_lattices(hs, n, cl);
+    return keep_bytes(cl, n);
 }
 
 // Lattice h takes the next `blocks` blocks of the launch a.
@@ -576,14 +519,18 @@ void launch_diag(lbm_sim *const *hs, int n, hipStream_t s)
 // One batched step for lattices hs[0..n) of the same physics, storage and
 // permeability form (diagonal or full tensor):
 // [colour pass,] step kernel, [diagnostics second stage].  The entries beyond n
-// of the arguments are not set: no kernel reads them.
-lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
+// of the arguments are not set: no kernel reads them.  keep: group_keep of all
+// the groups of this step, together.
+lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n, double keep)
 {
     const lbm_sim *h0 = hs[0];
     int flags[MAXB];
     double nuc[MAXB];
     lbm_sim *dhs[MAXB];
     int ndiag = 0;
+    CacheLattice cl[MAXB];
+    cache_lattices(hs, n, cl);
+    const int cache = cache_policy(cl, n, keep);
     for (int i = 0; i < n; ++i) {
         const lbm_sim *h = hs[i];
         const long long t = h->steps + 1;
@@ -606,14 +553,13 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n)
             if (flags[i] & 2) add_lattice(g.am, h, h->nblocks, flags[i]);
             st = st || h->d.A != 0.0;
         }
-        fs_launcher(h0->d.storage, h0->host.full_tensor != 0, st, cache_policy(hs, n))(g, h0->stream);
+        fs_launcher(h0->d.storage, h0->host.full_tensor != 0, st, cache)(g, h0->stream);
     } else {
         BatchArgs a;
         a.n = a.total_blocks = 0;
         // every lattice's range starts on a whole XCD row group (row_group_remap)
         for (int i = 0; i < n; ++i)
             add_lattice(a, hs[i], (hs[i]->nblocks + XCD_GROUP - 1) / XCD_GROUP * XCD_GROUP, flags[i], nuc[i]);
-        const int cache = cache_policy(hs, n);
         if (h0->d.physics == LBM_IMMISCIBLE) colour_launcher(h0->d.storage, cache)(a, a.total_blocks, h0->stream);
         step_launcher(h0->d.physics, h0->d.storage, h0->host.full_tensor != 0, h0->host.ms != nullptr, cache)(
             a, a.total_blocks, h0->stream);
@@ -1011,7 +957,7 @@ lbm_status lbm_step(lbm_t h, int nsteps)
     for (int s = 0; s < nsteps; ++s) {
         const bool last = s + 1 == nsteps;
         lbm_sim *one[1] = {h};
-        const lbm_status st = launch_batch_step(one, &last, 1);
+        const lbm_status st = launch_batch_step(one, &last, 1, group_keep(one, 1));
         if (st) return st;
     }
     return LBM_OK;
@@ -1033,9 +979,9 @@ lbm_status lbm_step_batch(lbm_t *hs, const int *nsteps, int n)
     if (hipSetDevice(hs[0]->device) != hipSuccess) return LBM_EDEVICE;
     lbm_sim *grp[MAXB];
     bool last[MAXB];
-    for (int s = 0; s < maxs; ++s) {
-        // group the lattices still running by (physics, storage, permeability
-        // form, further solutes)
+    // f(k) for every group of k lattices (grp, last) that take step s: grouped by
+    // (physics, storage, permeability form, further solutes)
+    const auto for_step_groups = [&](int s, auto &&f) -> lbm_status {
         for (int phys = LBM_SINGLE; phys <= LBM_FREESURF; ++phys)
             for (int grp_key = 0; grp_key < 4 * (LBM_F16_SPLIT + 1); ++grp_key) {
                 const int stg = grp_key >> 2, ft = grp_key & 1, ms = (grp_key >> 1) & 1;
@@ -1048,16 +994,32 @@ lbm_status lbm_step_batch(lbm_t *hs, const int *nsteps, int n)
                     grp[k] = h;
                     last[k] = s + 1 == nsteps[i];
                     if (++k == MAXB) {
-                        const lbm_status st = launch_batch_step(grp, last, k);
+                        const lbm_status st = f(k);
                         if (st) return st;
                         k = 0;
                     }
                 }
                 if (k) {
-                    const lbm_status st = launch_batch_step(grp, last, k);
+                    const lbm_status st = f(k);
                     if (st) return st;
                 }
             }
+        return LBM_OK;
+    };
+    double keep = 0.0;
+    for (int s = 0; s < maxs; ++s) {
+        // the groups change only where a lattice has had its steps
+        bool changed = s == 0;
+        for (int i = 0; i < n; ++i) changed = changed || nsteps[i] == s;
+        if (changed) {
+            keep = 0.0;
+            for_step_groups(s, [&](int k) {
+                keep += group_keep(grp, k);
+                return LBM_OK;
+            });
+        }
+        const lbm_status st = for_step_groups(s, [&](int k) { return launch_batch_step(grp, last, k, keep); });
+        if (st) return st;
     }
     return LBM_OK;
 }
