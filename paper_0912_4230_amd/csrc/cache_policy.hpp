@@ -38,53 +38,77 @@ enum {
 // what the choice depends on, per lattice of a launch
 struct CacheLattice {
     int physics, storage, nx;
+    int solutes;            // of the miscible model, else 1
     bool links, tensor;     // an obstacle mask; a full permeability tensor
     double cells, bytes;    // bytes: the populations (and split masses), both copies
+    double medium;          // bytes of the other fields that a step reads
 };
 
 // Cache policy of the populations in a step of these lattices (results are
 // bitwise the same under all three).  us per step, FP32 miscible unless named,
 // CACHE_STREAM / CACHE_REUSE / CACHE_KEEP:
 //
-// KEEP, when all the launch's populations (both copies) fit in the memory-side
-// cache (256 MB): a step then reads what the last one left there, where
-// non-temporal stores send it to memory.
+// KEEP, when all that the launch reads, the populations of both copies and the
+// medium, fits in the memory-side cache (256 MiB): a step then reads what the last
+// one left there, where non-temporal stores send it to memory.
 //   61^3 (69 MB) 15.4 / 15.7 / 13.6, 83^3 (174 MB) 40 / 39 / 32.6, 94^3 (252 MB)
 //   57 / 56 / 46, 98^3 (286 MB) 66 / 63 / 67; 70^3 BF16 (52 MB) 15.3 / 16.1 /
 //   14.4, 110^3 BF16 (202 MB) 47 / 46 / 41, 120^3 BF16 (263 MB) 59 / 57 / 60;
 //   two-fluid 80^3 36 / 37 / 30; channel FP64 64^3 17 / 18 / 14.
+// The end is sharp.  As gain over STREAM in percent, at MB of populations and
+// medium: BF16 deviations 243 16, 259 12, 265 -1, 271 -2; with a tensor 263 20, 268 0,
+// 282 -5; obstacles 250 22, 265 -1; FP16 split 254 25, 265 17, 278 -6; tensor 258 14,
+// 273 -3; obstacles 269 12, 284 -1; FP32 263 11, tensor 265 7, 274 3, obstacles and
+// tensor 282 5 (REUSE 11); FP64 tensor 264 8, 275 6, 282 -1.  The line lies at 264 MB
+// for the deviations, at 270 else, and at 256 of populations (BF16 channel without
+// medium planes 269 MB: REUSE 23, KEEP 20 to 26, by the workspace's place in memory).
 // Lattices that the L2s (32 MB) hold in part step as fast or faster under STREAM:
 //   48^3 9.6 / 10.2 / 10.7, 58^3 12.0 / 13.4 / 12.6, 64^3 BF16 9.2 / 10.5 / 10.4;
 // the line lies at 62 MB in the miscible model in FP32 and FP64 (96 MB with rows
-// of whole lines: 64^3, 80 MB, 14.4 / 15.9 / 14.8), at 50 MB else.  The smallest
-// gain again (32^3 FP64 channel, 10 MB, 6.6 / 6.6 / 6.0; 64^3 BF16 channel, 20
-// MB, 8.0 / 7.3 / 7.0; miscible 32^3, 10 MB, 7.9 / 7.9 / 7.7, but 40^3, 20 MB,
-// 8.3 / 8.9 / 9.0).
+// of whole lines: 64^3, 80 MB, 14.4 / 15.9 / 14.8), at 40 MB in its 16-bit forms
+// (1024 blocks, four per CU; FP16 deviations 68 x 47 x 78, 38 MB, 9.6 / 10.5 / 9.9,
+// 98 x 50 x 56, 42 MB, 12.7 / 13.5 / 11.3, 46 x 105 x 64, 47 MB, 13.5 / 14.2 / 11.8,
+// tensor 61 x 58 x 76, 41 MB, 14.4 / 15.2 / 13.2, BF16 with obstacles 67 x 64 x 72, 47
+// MB, 14.9 / 13.6 / 11.6), at 50 MB else.  The smallest gain again (32^3 FP64
+// channel, 10 MB, 6.6 / 6.6 / 6.0; 64^3 BF16 channel, 20 MB, 8.0 / 7.3 / 7.0; miscible
+// 32^3, 10 MB, 7.9 / 7.9 / 7.7, but 40^3, 20 MB, 8.3 / 8.9 / 9.0).
 //
 // REUSE, when lines are read by two waves: rows that are not whole lines put
-// most lines across a wave boundary (243 x 251 x 238 970 / 935, tensor 1075 /
-// 997; 250^3 988 / 936; 131^3 two-fluid 142 / 135, BF16 93 / 87; channel 150^3
-// FP64 201 / 190; where rows are whole lines 256^3 945 / 970, 128^3 two-fluid
-// 122 / 128); bounced links read a line once more (10% obstacles 256^3 1120 /
-// 1035, BF16 567 / 553).  The paired 16-bit planes of the miscible model gain
-// only where rows are not whole sectors of 32 bytes (tensor 243 x 251 x 238 BF16
-// 562 / 546; 200^3 BF16 254 / 255), the split forms among them only in larger
-// lattices (251^3 BF16 split 621 / 608, 101 x 310 x 299 FP16 split 372 / 365, 200^3
-// with 10% obstacles 364 / 354, but 155 x 151 x 140 136.8 / 139.0: the line lies
-// between, at 6M cells).  The FP32 tensor step gains with whole lines too where
-// it is larger still (224^3 719 / 698, 256^3 1050 / 1025, 320 x 256 x 256 1343 /
-// 1302, but 128 x 256 x 300 603 / 611, 192^3 417 / 439, 128^3 125 / 136: 10.5M
-// cells).
+// most lines across a wave boundary (FP32 243 x 251 x 238 970 / 935, 250^3 988 / 936;
+// 131^3 two-fluid 142 / 135, BF16 93 / 87; channel 150^3 FP64 201 / 190; where rows
+// are whole lines 256^3 945 / 970, 128^3 two-fluid 122 / 128); bounced links read a
+// line once more (10% obstacles 256^3 1120 / 1035, BF16 567 / 553).  The single-fluid
+// and two-fluid steps and the miscible one in FP32 and FP64 gain over the whole
+// range; the others by size, as gain of REUSE over STREAM in percent:
+//   deviations, rows not whole sectors of 32 bytes (whole ones: 200^3 254 / 255):
+//     331 MB of populations 4.3, 454 MB 4.2, 551 MB 1.5, 603 MB 0, 630 MB -1.2, 0.7
+//     to 1.2 GB -1 to -2, 1.6 GB (planes of 41 MB) 0, 2.2 GB 1.4, 4.2 GB 5.5
+//   with a tensor: 307 MB 1, 415 MB -1.7, 0.54 to 0.95 GB -5, 1.3 GB (34 MB) -1.5,
+//     1.4 GB (38 MB) 2.1, 2.0 GB 2.9; and obstacles: 367 MB 3.3, 522 MB -3.3, 0.9 GB
+//     -3.7, 1.07 GB (28 MB) -2.7, 1.17 GB (31 MB) 4, 1.4 GB 5.9
+//   split: 14 MB planes -2.4, 26 MB -2.7, 32 MB -2, 35 MB -0.4, 36.3 MB 2, 114 MB 2.3;
+//     tensor: 8 to 16 MB -3 to -5, 25 MB -0.8, 26.5 MB 2.1, 33 MB 1.9; obstacles
+//     from 23 MB 1.9; two solutes 16 MB -1.3, 24 MB 0.3, 42 MB 2.2
+//   FP32 tensor: 0.35 GB 4.1, 0.72 GB 2.3, 0.89 GB -2.1, 1.2 GB -1.9, 1.6 GB -1.9, 2.3
+//     GB (30 MB) 0.3, 2.4 GB (32 MB) 1.2, 4.2 GB (55 MB) 7.9; FP64 0.46 GB 2.4, 0.88
+//     GB -4.9, 1.7 GB -2.6, 2.8 GB (36 MB) 1.9; whole lines in FP32: 17 to 25 MB -5, 35
+//     MB 0, 39 MB (128 x 256 x 300) -1.3, 54 MB 2.5, 67 MB 3.1
+// So it gains again where a plane no longer fits in the L2s (32 MB together), and
+// up to two or three times the memory-side cache.  The obstacles' gain is that of
+// a tenth of the cells; BF16 and FP16 with a fiftieth range from -2 to 1.
 //
 // The free-surface step leaves the gas cells out; KEEP from 50 to 256 MB of
 // populations there, STREAM else (us, whole step, STREAM / KEEP: 48^3 FP32 17 MB
 // 24.8 / 25.2, 61 x 71 x 81 53 MB 30.0 / 29.4, 101 x 100 x 97 149 MB 34.8 / 32.9,
 // FP16 split 82 MB 33.2 / 31.1, 110^3 202 MB 36.4 / 34.3, 128^3 BF16 159 MB 33.6 /
 // 33.8; 128^3 319 MB 44.5 / 45.2, 200 x 190 x 180 1040 MB 130 / 139); plain loads
-// alone gain nothing.
+// alone gain nothing.  21 boxes of odd sizes from 55 to 256 MB: KEEP 2 to 14% faster
+// in FP32 and BF16, 4 to 20% in FP16 split.
 //
-// The lattices of a batch share the launch: their bytes add up, and the larger
-// part of their cells decides between REUSE and STREAM.
+// The lattices of a batch share the launch: their bytes and planes add up (BF16,
+// seven lattices with 12.7M miscible cells, the largest 6.5M, STREAM 588 / REUSE 559;
+// 9.4M of 187^3, 75^3 and others 428 / 415), and the larger part of their cells decides
+// between REUSE and STREAM.
 //
 // lbm_step_batch advances groups of lattices one after the other, in launches of
 // their own, and a group finds what its last step left only if the others have
@@ -96,22 +120,28 @@ struct CacheLattice {
 // Streaming where only one of the two would keep loses: 64^3 90^3 35.6 / 40.0, 96^3
 // 80^3 72.5 / 75.2.
 
-constexpr double CACHE_MB = 1e6, CACHE_SIDE = 256 * CACHE_MB;
+constexpr double CACHE_MB = 1e6, CACHE_SIDE = 270 * CACHE_MB;
 
-// the bytes of a launch, and from where on its step gains by KEEP or REUSE
+// the bytes of a launch's populations and of all that it reads (free surface: the
+// populations, of which half or so are gas), and between which its step gains by KEEP
 struct CacheLaunch {
-    double bytes, low;
+    double bytes, all, low, end;
 };
 
 inline CacheLaunch cache_launch(const CacheLattice *l, int n)
 {
-    CacheLaunch a = {0.0, 50 * CACHE_MB};
+    CacheLaunch a = {0.0, 0.0, 50 * CACHE_MB, CACHE_SIDE};
     bool whole_lines = true;
     for (int i = 0; i < n; ++i) {
         whole_lines = whole_lines && l[i].nx * storage_bytes(l[i].storage) % 128 == 0;
         a.bytes += l[i].bytes;
+        a.all += l[i].bytes + (l->physics == LBM_FREESURF ? 0.0 : l[i].medium);
     }
-    if (l->physics == LBM_MISCIBLE && !paired_storage(l->physics, l->storage)) a.low = (whole_lines ? 96 : 62) * CACHE_MB;
+    if (l->physics == LBM_MISCIBLE) {
+        const bool paired = paired_storage(l->physics, l->storage);
+        a.low = (paired ? 40 : (whole_lines ? 96 : 62)) * CACHE_MB;
+        if (paired && !split_storage(l->storage)) a.end = 264 * CACHE_MB;
+    }
     return a;
 }
 
@@ -121,7 +151,25 @@ inline double keep_bytes(const CacheLattice *l, int n)
 {
     const CacheLaunch a = cache_launch(l, n);
     const double tiny = (l->physics == LBM_FREESURF ? 0 : (l->physics == LBM_SINGLE ? 24 : 12)) * CACHE_MB;
-    return a.bytes <= tiny || (a.bytes >= a.low && a.bytes <= CACHE_SIDE) ? a.bytes : 0.0;
+    return a.bytes <= tiny || (a.bytes >= a.low && a.bytes <= 256 * CACHE_MB && a.all <= a.end) ? a.all : 0.0;
+}
+
+// Does a lattice beyond the memory-side cache step faster under REUSE than under
+// STREAM, in a launch of so many cells?
+inline bool reuse_pays(const CacheLattice &c, double cells)
+{
+    const bool paired = paired_storage(c.physics, c.storage);
+    const size_t word = storage_bytes(c.storage) * (paired ? 2 : 1);
+    const bool shared = c.nx * word % (paired ? 32 : 128) != 0 || c.links;
+    const double plane = cells * double(word) / CACHE_MB, bytes = c.bytes / CACHE_MB;
+    if (!shared) return c.tensor && c.storage == LBM_F32 && plane > 42;
+    if (c.physics != LBM_MISCIBLE) return true;
+    if (split_storage(c.storage)) return plane > (c.tensor || c.links || c.solutes > 1 ? 24 : 35);
+    if (paired) {
+        if (c.solutes > 1 || (c.links && !c.tensor)) return true;
+        return plane > (c.tensor && c.links ? 30 : 35) || bytes <= (c.tensor ? 400 : 600);
+    }
+    return !c.tensor || c.links || c.solutes > 1 || plane > 29 || bytes <= 740;
 }
 
 // keep: keep_bytes of all the launches of the step, together
@@ -129,19 +177,12 @@ inline int cache_policy(const CacheLattice *l, int n, double keep)
 {
     if (keep <= CACHE_SIDE && keep_bytes(l, n) > 0.0) return CACHE_KEEP;
     if (l->physics == LBM_FREESURF) return CACHE_STREAM;
-    double cells = 0, reuse = 0;
-    for (int i = 0; i < n; ++i) {
-        const CacheLattice &c = l[i];
-        const bool paired = paired_storage(c.physics, c.storage);
-        const size_t row = c.nx * storage_bytes(c.storage) * (paired ? 2 : 1);
-        const bool shared = row % (paired ? 32 : 128) != 0 || c.links;
-        cells += c.cells;
-        if (paired ? shared && (!split_storage(c.storage) || c.cells > 6e6)
-                   : shared || (c.tensor && c.storage == LBM_F32 && c.cells > 10.5e6))
-            reuse += c.cells;
-    }
     const CacheLaunch a = cache_launch(l, n);
-    return a.bytes > a.low && 2 * reuse > cells ? CACHE_REUSE : CACHE_STREAM;
+    double cells = 0, reuse = 0;
+    for (int i = 0; i < n; ++i) cells += l[i].cells;
+    for (int i = 0; i < n; ++i)
+        if (reuse_pays(l[i], cells)) reuse += l[i].cells;
+    return a.bytes > 50 * CACHE_MB && a.bytes > a.low && 2 * reuse > cells ? CACHE_REUSE : CACHE_STREAM;
 }
 
 }  // namespace plbm

@@ -470,10 +470,13 @@ CacheLattice cache_lattice(const lbm_sim *h)
     c.physics = d->physics;
     c.storage = d->storage;
     c.nx = d->nx;
+    c.solutes = 1 + extra_species(d);
     c.links = h->host.links != nullptr;
     c.tensor = h->host.full_tensor != 0;
     c.cells = h->host.ncell;
     c.bytes = double((d->physics == LBM_FREESURF ? h->lay.fs : h->lay.total) - h->lay.f0);
+    const int planes = (h->host.uniform_eps ? 0 : 1) + (c.tensor ? 7 : (h->host.uniform_kinv ? 0 : 3)) + (h->host.rho1 ? 1 : 0);
+    c.medium = c.cells * double(planes * real_bytes(d->storage) + (c.links ? sizeof(uint32_t) : 0));
     return c;
 }
 

@@ -36,3 +36,53 @@ def test_free_surface_counts():
     fs, tank = [lattice("freesurf", "f32", (100, 100, 90))], [lattice("single", "f32", (100, 100, 90))]
     assert policies([fs]) == [KEEP] and policies([tank]) == [KEEP]
     assert policies([fs, tank]) == [STREAM, REUSE]
+
+
+# (storage, shape, options, policy): alone, on both sides of every line of the rule
+LINES = [
+    # 16-bit miscible forms keep from 40 MB on
+    ("bf16", (65, 63, 64), {}, STREAM), ("bf16", (67, 64, 72), {}, KEEP), ("f16", (46, 105, 64), {}, KEEP),
+    ("f16", (67, 64, 72), {"links": True}, KEEP), ("bf16", (61, 58, 76), {"tensor": True}, KEEP),
+    # up to what fits with the medium
+    ("bf16", (151, 106, 96), {}, KEEP), ("bf16", (79, 106, 199), {}, REUSE), ("bf16", (115, 115, 115), {"uniform": True}, KEEP),
+    ("bf16", (164, 82, 106), {"tensor": True}, KEEP), ("f16", (109, 88, 162), {"tensor": True}, REUSE),
+    ("bf16", (154, 133, 71), {"links": True}, KEEP), ("bf16", (138, 125, 94), {"links": True}, REUSE),
+    ("f16s", (142, 118, 86), {}, KEEP), ("f16s", (122, 94, 132), {}, STREAM),
+    ("f16s", (135, 94, 102), {"tensor": True}, KEEP), ("bf16s", (74, 145, 139), {"tensor": True}, STREAM),
+    ("f32", (94, 94, 94), {}, KEEP), ("f32", (98, 98, 98), {}, REUSE), ("f32", (85, 122, 76), {"tensor": True}, KEEP),
+    ("f32", (97, 108, 79), {"tensor": True, "links": True}, REUSE), ("f64", (82, 51, 94), {"tensor": True}, KEEP),
+    ("f64", (55, 83, 92), {"tensor": True}, REUSE),
+    ("f32", (59, 58, 59), {}, STREAM), ("f32", (61, 61, 61), {}, KEEP), ("f32", (64, 64, 64), {}, STREAM),
+    # deviations: plain loads up to 600 MB and from planes of 35 MB on
+    ("f16", (177, 133, 154), {}, REUSE), ("f16", (212, 169, 122), {}, STREAM), ("f16", (243, 97, 228), {}, STREAM),
+    ("bf16", (187, 199, 213), {}, STREAM), ("bf16", (217, 208, 208), {}, REUSE), ("bf16", (200, 200, 200), {}, STREAM),
+    ("bf16", (212, 169, 122), {"species": 2}, REUSE), ("f16", (243, 97, 228), {"links": True}, REUSE),
+    # with a tensor up to 400 MB; with obstacles too from planes of 30 MB on
+    ("bf16", (147, 114, 150), {"tensor": True}, REUSE), ("f16", (133, 135, 202), {"tensor": True}, STREAM),
+    ("bf16", (187, 199, 213), {"tensor": True}, STREAM), ("bf16", (243, 251, 238), {"tensor": True}, REUSE),
+    ("f16", (122, 275, 167), {"tensor": True, "links": True}, STREAM),
+    ("f16", (201, 211, 166), {"tensor": True, "links": True}, STREAM),
+    ("bf16", (165, 241, 203), {"tensor": True, "links": True}, REUSE),
+    # split forms from planes of 35 MB on, 24 MB with more arithmetic
+    ("bf16s", (189, 233, 150), {}, STREAM), ("bf16s", (187, 199, 213), {}, STREAM), ("f16s", (101, 310, 299), {}, REUSE),
+    ("bf16s", (187, 199, 213), {"tensor": True}, REUSE), ("f16s", (155, 151, 140), {"tensor": True}, STREAM),
+    ("f16s", (200, 200, 200), {"links": True}, REUSE), ("f16s", (160, 160, 160), {"links": True}, STREAM),
+    ("bf16s", (183, 129, 172), {"species": 2}, STREAM), ("f16s", (230, 212, 214), {"species": 2}, REUSE),
+    # FP32 and FP64: always, but with a tensor and no obstacles not between 740 MB and planes of 29 MB
+    ("f32", (163, 207, 181), {}, REUSE), ("f32", (256, 256, 256), {}, STREAM), ("f32", (256, 256, 256), {"links": True}, REUSE),
+    ("f32", (125, 120, 158), {"tensor": True}, REUSE), ("f32", (95, 226, 184), {"tensor": True}, STREAM),
+    ("f32", (243, 251, 238), {"tensor": True}, REUSE), ("f32", (95, 226, 184), {"tensor": True, "links": True}, REUSE), ("f32", (193, 228, 119), {"tensor": True}, STREAM),
+    ("f64", (130, 94, 62), {"tensor": True}, REUSE), ("f64", (171, 114, 128), {"tensor": True}, STREAM),
+    ("f64", (111, 191, 214), {"tensor": True}, REUSE),
+    ("f32", (192, 203, 224), {"tensor": True}, STREAM), ("f32", (256, 224, 192), {"tensor": True}, REUSE),
+]
+
+
+@pytest.mark.parametrize("storage,shape,options,want", LINES)
+def test_lines_of_the_miscible_step(storage, shape, options, want):
+    assert policies([[lattice("miscible", storage, shape, **options)]]) == [want]
+
+
+def test_planes_of_a_launch_add_up():
+    a, b = lattice("miscible", "bf16", (187, 187, 187)), lattice("miscible", "bf16", (162, 162, 162))
+    assert policies([[a]]) == policies([[b]]) == [STREAM] and policies([[a, b]]) == [REUSE]
