@@ -496,12 +496,12 @@ double group_keep(lbm_sim *const *hs, int n)
 // Lattice h takes the next `blocks` blocks of the launch a.
 void add_lattice(BatchArgs &a, const lbm_sim *h, int blocks, int flags = 0, double nuc = 0.0)
 {
-    BatchEntry &e = a.e[a.n++];
+    BatchEntry &e = a.e[a.n];
     e.lat = h->dev;
     e.fs = h->host.fs;
     e.nuc = nuc;
     e.first = a.total_blocks;
-    e.end = a.total_blocks += blocks;
+    e.end = a.end[a.n++] = a.total_blocks += blocks;
     e.flags = flags;
     e.pad = 0;
 }
