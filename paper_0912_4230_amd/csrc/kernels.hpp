@@ -1524,17 +1524,19 @@ __global__ __launch_bounds__(BLOCK) void k_colour(const BatchArgs a)
 }
 
 // Second stage of the diagnostics: the per-block partials of a lattice summed in
-// a fixed order.  A lattice of more than DIAG_ROWS of them takes two launches:
+// a fixed order.  A lattice of more than DIAG_ONE of them takes two launches:
 // first one block per DIAG_ROWS rows of partials, which leaves its sums in the
 // first of them, then one block over those; a smaller one takes only the last
 // (one block over 65,536 rows of a 256^3 lattice read 4.7 MB by itself: 112 us,
-// in two launches 6 + 5 us).
+// in two launches 6 + 5 us).  Set-up, in us, by one launch / two: 1089 rows (66 x 66
+// x 64 two-fluid) 45 / 59, 1340 42 / 43, 2000 75.5 / 76.5, 2848 85 / 85, 4105 97 /
+// 96, 5199 91 / 88, 13184 150 / 139: the line lies at 3072.
 // Which a lattice takes depends on its own size alone, so its sums do not
 // depend on the batch it steps in.
-constexpr int DIAG_ROWS = 1024;
+constexpr int DIAG_ROWS = 1024, DIAG_ONE = 3072;
 __host__ __device__ inline int diag_chunks(int nblocks)
 {
-    return nblocks > DIAG_ROWS ? (nblocks + DIAG_ROWS - 1) / DIAG_ROWS : 0;
+    return nblocks > DIAG_ONE ? (nblocks + DIAG_ROWS - 1) / DIAG_ROWS : 0;
 }
 
 // the sums of partial rows first, first + stride, ... (n of them) on this thread
