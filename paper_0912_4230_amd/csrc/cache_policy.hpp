@@ -89,10 +89,11 @@ struct CacheLattice {
 //   split: 14 MB planes -2.4, 26 MB -2.7, 32 MB -2, 35 MB -0.4, 36.3 MB 2, 114 MB 2.3;
 //     tensor: 8 to 16 MB -3 to -5, 25 MB -0.8, 26.5 MB 2.1, 33 MB 1.9; obstacles
 //     from 23 MB 1.9; two solutes 16 MB -1.3, 24 MB 0.3, 42 MB 2.2
-//   FP32 tensor: 0.35 GB 4.1, 0.72 GB 2.3, 0.89 GB -2.1, 1.2 GB -1.9, 1.6 GB -1.9, 2.3
-//     GB (30 MB) 0.3, 2.4 GB (32 MB) 1.2, 4.2 GB (55 MB) 7.9; FP64 0.46 GB 2.4, 0.88
-//     GB -4.9, 1.7 GB -2.6, 2.8 GB (36 MB) 1.9; whole lines in FP32: 17 to 25 MB -5, 35
-//     MB 0, 39 MB (128 x 256 x 300) -1.3, 54 MB 2.5, 67 MB 3.1
+//   FP32 tensor: 0.35 GB 4.1, 0.58 GB 2 to 3, 0.62 GB -0.2 to -2.4, 0.71 GB -5 to 2.3, 0.89
+//     GB -2.1, 1.2 GB -1.9, 1.6 GB -1.9, 2.3 GB (30 MB) 0.3, 2.4 GB (32 MB) 1.2, 4.2 GB (55
+//     MB) 7.9; FP64 0.46 GB 2.4, 0.52 GB -0.4, 0.59 GB -1.7, 0.88 GB -4.9, 1.7 GB -2.6, 2.8 GB
+//     (36 MB) 1.9; whole lines in FP32: 17 to 25 MB -5, 35 MB 0, 39 MB (128 x 256 x 300)
+//     -1.3, 54 MB 2.5, 67 MB 3.1
 // So it gains again where a plane no longer fits in the L2s (32 MB together), and
 // up to two or three times the memory-side cache.  The obstacles' gain is that of
 // a tenth of the cells; BF16 and FP16 with a fiftieth range from -2 to 1.
@@ -169,7 +170,7 @@ inline bool reuse_pays(const CacheLattice &c, double cells)
         if (c.solutes > 1 || (c.links && !c.tensor)) return true;
         return plane > (c.tensor && c.links ? 30 : 35) || bytes <= (c.tensor ? 400 : 600);
     }
-    return !c.tensor || c.links || c.solutes > 1 || plane > 29 || bytes <= 740;
+    return !c.tensor || c.links || c.solutes > 1 || plane > 29 || bytes <= (c.storage == LBM_F64 ? 500 : 600);
 }
 
 // keep: keep_bytes of all the launches of the step, together

@@ -68,11 +68,14 @@ LINES = [
     ("bf16s", (187, 199, 213), {"tensor": True}, REUSE), ("f16s", (155, 151, 140), {"tensor": True}, STREAM),
     ("f16s", (200, 200, 200), {"links": True}, REUSE), ("f16s", (160, 160, 160), {"links": True}, STREAM),
     ("bf16s", (183, 129, 172), {"species": 2}, STREAM), ("f16s", (230, 212, 214), {"species": 2}, REUSE),
-    # FP32 and FP64: always, but with a tensor and no obstacles not between 740 MB and planes of 29 MB
+    # FP32 and FP64: always, but with a tensor and no obstacles not between 600 MB (FP64 500)
+    # and planes of 29 MB
     ("f32", (163, 207, 181), {}, REUSE), ("f32", (256, 256, 256), {}, STREAM), ("f32", (256, 256, 256), {"links": True}, REUSE),
-    ("f32", (125, 120, 158), {"tensor": True}, REUSE), ("f32", (95, 226, 184), {"tensor": True}, STREAM),
+    ("f32", (123, 125, 127), {"tensor": True}, REUSE), ("f32", (49, 293, 160), {"tensor": True}, STREAM),
+    ("f32", (95, 226, 184), {"tensor": True}, STREAM),
     ("f32", (243, 251, 238), {"tensor": True}, REUSE), ("f32", (95, 226, 184), {"tensor": True, "links": True}, REUSE), ("f32", (193, 228, 119), {"tensor": True}, STREAM),
-    ("f64", (130, 94, 62), {"tensor": True}, REUSE), ("f64", (171, 114, 128), {"tensor": True}, STREAM),
+    ("f64", (130, 94, 62), {"tensor": True}, REUSE), ("f64", (75, 111, 105), {"tensor": True}, STREAM),
+    ("f64", (171, 114, 128), {"tensor": True}, STREAM),
     ("f64", (111, 191, 214), {"tensor": True}, REUSE),
     ("f32", (192, 203, 224), {"tensor": True}, STREAM), ("f32", (256, 224, 192), {"tensor": True}, REUSE),
 ]
