@@ -120,8 +120,16 @@ struct CacheLattice {
 // 80^3 80^3 51.7 / 49.2, 90^3 64^3 55.1 / 52.4, BF16 110^3 110^3 75.7 / 71.3.
 // Streaming where only one of the two would keep loses: 64^3 90^3 35.6 / 40.0, 96^3
 // 80^3 72.5 / 75.2.
+// Plain loads do push kept lines out.  Beside kept groups the others stream, unless
+// they have more than 4.5 times their bytes: then nothing is kept.  us per step, both /
+// the others streamed / nothing kept, by that ratio: 2.1 BF16 98 95 56 106 60 (the
+// second and fifth two-fluid) 120.2 / 116 / 117, 3.1 FP32 50 125 71 54 107.1 / 100.0 /
+// 102.3, 4.3 BF16 100 161 119.4 / 115 / 117.5, 5 BF16 121 77 117 63 96 143 65 272.6 / 272.6 /
+// 268, 8.6 BF16 120 104 63 126 64 112 190 424 / 435 / 422, 10 FP32 83 178 226.6 / 230.7 / 221,
+// 18 FP32 180 72 95 126 55 108 626 / 660 / 622.
 
 constexpr double CACHE_MB = 1e6, CACHE_SIDE = 270 * CACHE_MB;
+constexpr double CACHE_BESIDE = 4.5;   // REUSE bytes beside a kept byte, from where on keeping loses
 
 // the bytes of a launch's populations and of all that it reads (free surface: the
 // populations, of which half or so are gas), and between which its step gains by KEEP
@@ -173,17 +181,34 @@ inline bool reuse_pays(const CacheLattice &c, double cells)
     return !c.tensor || c.links || c.solutes > 1 || plane > 29 || bytes <= (c.storage == LBM_F64 ? 500 : 600);
 }
 
-// keep: keep_bytes of all the launches of the step, together
-inline int cache_policy(const CacheLattice *l, int n, double keep)
+inline bool launch_reuses(const CacheLattice *l, int n)
 {
-    if (keep <= CACHE_SIDE && keep_bytes(l, n) > 0.0) return CACHE_KEEP;
-    if (l->physics == LBM_FREESURF) return CACHE_STREAM;
     const CacheLaunch a = cache_launch(l, n);
     double cells = 0, reuse = 0;
     for (int i = 0; i < n; ++i) cells += l[i].cells;
     for (int i = 0; i < n; ++i)
         if (reuse_pays(l[i], cells)) reuse += l[i].cells;
-    return a.bytes > 50 * CACHE_MB && a.bytes > a.low && 2 * reuse > cells ? CACHE_REUSE : CACHE_STREAM;
+    return l->physics != LBM_FREESURF && a.bytes > 50 * CACHE_MB && a.bytes > a.low && 2 * reuse > cells;
+}
+
+// What the launches of one step would keep and, the others, read by plain loads.
+struct CacheStep {
+    double keep, reuse;
+};
+
+inline void add_launch(CacheStep &s, const CacheLattice *l, int n)
+{
+    const double k = keep_bytes(l, n);
+    s.keep += k;
+    if (k == 0.0 && launch_reuses(l, n)) s.reuse += cache_launch(l, n).all;
+}
+
+// The policy of a launch in a step s (its own launch counted).
+inline int cache_policy(const CacheLattice *l, int n, const CacheStep &s)
+{
+    const bool keeps = s.keep > 0.0 && s.keep <= CACHE_SIDE && s.reuse <= CACHE_BESIDE * s.keep;
+    if (keeps && keep_bytes(l, n) > 0.0) return CACHE_KEEP;
+    return !keeps && launch_reuses(l, n) ? CACHE_REUSE : CACHE_STREAM;
 }
 
 }  // namespace plbm

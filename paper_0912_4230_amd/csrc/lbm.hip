@@ -485,12 +485,12 @@ void cache_lattices(lbm_sim *const *hs, int n, CacheLattice out[MAXB])
     for (int i = 0; i < n; ++i) out[i] = cache_lattice(hs[i]);
 }
 
-// the bytes a group would keep in the memory-side cache (keep_bytes)
-double group_keep(lbm_sim *const *hs, int n)
+// a group of a step, for the cache policies of the step's groups
+void add_group(CacheStep &step, lbm_sim *const *hs, int n)
 {
     CacheLattice cl[MAXB];
     cache_lattices(hs, n, cl);
-    return keep_bytes(cl, n);
+    add_launch(step, cl, n);
 }
 
 // Lattice h takes the next `blocks` blocks of the launch a.
@@ -522,9 +522,9 @@ void launch_diag(lbm_sim *const *hs, int n, hipStream_t s)
 // One batched step for lattices hs[0..n) of the same physics, storage and
 // permeability form (diagonal or full tensor):
 // [colour pass,] step kernel, [diagnostics second stage].  The entries beyond n
-// of the arguments are not set: no kernel reads them.  keep: group_keep of all
-// the groups of this step, together.
-lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n, double keep)
+// of the arguments are not set: no kernel reads them.  step: all the groups of
+// this step (add_group).
+lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n, const CacheStep &step)
 {
     const lbm_sim *h0 = hs[0];
     int flags[MAXB];
@@ -533,7 +533,7 @@ lbm_status launch_batch_step(lbm_sim *const *hs, const bool *last, int n, double
     int ndiag = 0;
     CacheLattice cl[MAXB];
     cache_lattices(hs, n, cl);
-    const int cache = cache_policy(cl, n, keep);
+    const int cache = cache_policy(cl, n, step);
     for (int i = 0; i < n; ++i) {
         const lbm_sim *h = hs[i];
         const long long t = h->steps + 1;
@@ -957,10 +957,12 @@ lbm_status lbm_step(lbm_t h, int nsteps)
     if (!h || nsteps < 0) return LBM_EINVAL;
     if (!h->ready) return LBM_ESTATE;
     if (hipSetDevice(h->device) != hipSuccess) return LBM_EDEVICE;
+    lbm_sim *one[1] = {h};
+    CacheStep step = {0.0, 0.0};
+    add_group(step, one, 1);
     for (int s = 0; s < nsteps; ++s) {
         const bool last = s + 1 == nsteps;
-        lbm_sim *one[1] = {h};
-        const lbm_status st = launch_batch_step(one, &last, 1, group_keep(one, 1));
+        const lbm_status st = launch_batch_step(one, &last, 1, step);
         if (st) return st;
     }
     return LBM_OK;
@@ -1009,19 +1011,19 @@ lbm_status lbm_step_batch(lbm_t *hs, const int *nsteps, int n)
             }
         return LBM_OK;
     };
-    double keep = 0.0;
+    CacheStep step = {0.0, 0.0};
     for (int s = 0; s < maxs; ++s) {
         // the groups change only where a lattice has had its steps
         bool changed = s == 0;
         for (int i = 0; i < n; ++i) changed = changed || nsteps[i] == s;
         if (changed) {
-            keep = 0.0;
+            step = {0.0, 0.0};
             for_step_groups(s, [&](int k) {
-                keep += group_keep(grp, k);
+                add_group(step, grp, k);
                 return LBM_OK;
             });
         }
-        const lbm_status st = for_step_groups(s, [&](int k) { return launch_batch_step(grp, last, k, keep); });
+        const lbm_status st = for_step_groups(s, [&](int k) { return launch_batch_step(grp, last, k, step); });
         if (st) return st;
     }
     return LBM_OK;

@@ -19,8 +19,14 @@ SHIM = """
 using namespace plbm;
 extern "C" {
 size_t lattice_size() { return sizeof(CacheLattice); }
-double keep(const CacheLattice *l, int n) { return keep_bytes(l, n); }
-int policy(const CacheLattice *l, int n, double k) { return cache_policy(l, n, k); }
+void add(double *step, const CacheLattice *l, int n)
+{
+    CacheStep s = {step[0], step[1]};
+    add_launch(s, l, n);
+    step[0] = s.keep;
+    step[1] = s.reuse;
+}
+int policy(const CacheLattice *l, int n, const double *step) { return cache_policy(l, n, CacheStep{step[0], step[1]}); }
 }
 """
 
@@ -41,8 +47,6 @@ def _lib():
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_0912_4230_amd", "csrc"),
                     src, "-o", out], check=True)
     L = C.CDLL(out)
-    L.keep.restype = C.c_double
-    L.policy.argtypes = [C.c_void_p, C.c_int, C.c_double]
     L.lattice_size.restype = C.c_size_t
     assert L.lattice_size() == C.sizeof(CacheLattice)
     return L
@@ -64,5 +68,7 @@ def lattice(physics, storage, shape, links=False, tensor=False, species=1, unifo
 def policies(groups):
     """The policy of every group (a list of lattices) of a batch in one step."""
     arrays = [(CacheLattice * len(g))(*g) for g in groups]
-    keep = sum(_lib().keep(a, len(a)) for a in arrays)
-    return [_lib().policy(a, len(a), keep) for a in arrays]
+    step = (C.c_double * 2)()
+    for a in arrays:
+        _lib().add(step, a, len(a))
+    return [_lib().policy(a, len(a), step) for a in arrays]

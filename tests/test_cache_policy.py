@@ -89,3 +89,19 @@ def test_lines_of_the_miscible_step(storage, shape, options, want):
 def test_planes_of_a_launch_add_up():
     a, b = lattice("miscible", "bf16", (187, 187, 187)), lattice("miscible", "bf16", (162, 162, 162))
     assert policies([[a]]) == policies([[b]]) == [STREAM] and policies([[a, b]]) == [REUSE]
+
+
+@pytest.mark.parametrize("a,b,storage,want", [
+    # the others stream beside what is kept
+    ((50, 71, 54), (125,), "f32", [KEEP, STREAM]), ((100,), (161,), "bf16", [KEEP, STREAM]),
+    ((98, 56, 106), (95, 60), "bf16", [STREAM, KEEP]),
+    # with more than 4.5 times its bytes nothing is kept
+    ((49, 52), (161,), "f32", [REUSE, REUSE]), ((83,), (178,), "f32", [REUSE, REUSE]),
+    ((121, 117, 63, 143, 65), (77, 96), "bf16", [REUSE, REUSE]),
+])
+def test_plain_loads_beside_kept_groups(a, b, storage, want):
+    groups = _pair(a, b, storage)
+    for g in groups:
+        for c in g:         # the two-fluid lattices lie in a medium too
+            c.medium = c.cells * (16 + 4 * (g is groups[1]))
+    assert policies(groups) == want
