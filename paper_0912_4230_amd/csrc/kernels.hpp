@@ -113,10 +113,10 @@ __device__ inline const GL MsDev *ms_of(const LatDev *L)
 // fields are fetched with the parameter block's and not after them.  us per step,
 // a table per field against this: 32^3 FP64 channel 6.05 -> 5.7, 48^3 miscible
 // FP32 9.9 -> 9.6, 140 x 140 x 1 free surface 31.9 -> 30.7, 64^3 penetration
-// 23.9 -> 22.9.  Only the search for a block's lattice among more than 8 has a table
-// of its own, which it walks through in steps of 4 bytes and not of an entry: 60
-// lattices of 12^3 in FP32 26.7 -> 25.1 us per step, 64 channels of 16^3 19.1 -> 17.9
-// (up to 8 lattices the entries are as near: 3 to 8 of 49^3 to 177^3 0.1 to 0.3% faster).
+// 23.9 -> 22.9.  Only the search for a block's lattice has a table of its own, which
+// it walks through in steps of 4 bytes and not of an entry: 60 lattices of 12^3
+// in FP32 26.7 -> 25.1 us per step, 64 channels of 16^3 19.1 -> 17.9, 8 of 48^3 to
+// 52^3 64.4 -> 65.2.
 struct BatchEntry {
     const LatDev *lat;
     const void *fs;
@@ -193,11 +193,8 @@ __device__ inline int step_block(int b, int nb, const LatDev *L)
 __device__ inline int find_lattice(const BatchArgs &a, int gb)
 {
     int l = 0;
-    if (a.n <= 8) {
-        while (l + 1 < a.n && gb >= a.e[l].end) ++l;
-    } else {
+    if (__builtin_expect(a.n > 1, 0))   // a launch of one lattice runs past it (152 x 76 x 12 FP64 channel 7.9 -> 7.55 us)
         while (l + 1 < a.n && gb >= a.end[l]) ++l;
-    }
     return l;
 }
 
