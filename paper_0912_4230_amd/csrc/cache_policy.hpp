@@ -71,7 +71,9 @@ struct CacheLattice {
 // tensor 61 x 58 x 76, 41 MB, 14.4 / 15.2 / 13.2, BF16 with obstacles 67 x 64 x 72, 47
 // MB, 14.9 / 13.6 / 11.6), at 50 MB else.  The smallest gain again (32^3 FP64
 // channel, 10 MB, 6.6 / 6.6 / 6.0; 64^3 BF16 channel, 20 MB, 8.0 / 7.3 / 7.0; miscible
-// 32^3, 10 MB, 7.9 / 7.9 / 7.7, but 40^3, 20 MB, 8.3 / 8.9 / 9.0).
+// 32^3, 10 MB, 7.9 / 7.9 / 7.7, but 40^3, 20 MB, 8.3 / 8.9 / 9.0): up to 12 MB, the
+// single-fluid step up to 24 MB, in FP64 to 15 MB (13 MB 6.3 / 6.2 / 6.0, 19 MB 6.9 / 6.9 /
+// 7.3, 46 x 33 x 47, 22 MB, 7.1 / 7.2 / 7.9).
 //
 // REUSE, when lines are read by two waves: rows that are not whole lines put
 // most lines across a wave boundary (FP32 243 x 251 x 238 970 / 935, 250^3 988 / 936;
@@ -159,7 +161,8 @@ inline CacheLaunch cache_launch(const CacheLattice *l, int n)
 inline double keep_bytes(const CacheLattice *l, int n)
 {
     const CacheLaunch a = cache_launch(l, n);
-    const double tiny = (l->physics == LBM_FREESURF ? 0 : (l->physics == LBM_SINGLE ? 24 : 12)) * CACHE_MB;
+    const double tiny = (l->physics == LBM_FREESURF ? 0 : (l->physics != LBM_SINGLE ? 12 : (l->storage == LBM_F64 ? 15 : 24))) *
+                        CACHE_MB;
     return a.bytes <= tiny || (a.bytes >= a.low && a.bytes <= 256 * CACHE_MB && a.all <= a.end) ? a.all : 0.0;
 }
 

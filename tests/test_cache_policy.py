@@ -105,3 +105,13 @@ def test_plain_loads_beside_kept_groups(a, b, storage, want):
         for c in g:         # the two-fluid lattices lie in a medium too
             c.medium = c.cells * (16 + 4 * (g is groups[1]))
     assert policies(groups) == want
+
+
+@pytest.mark.parametrize("physics,storage,shape,want", [
+    ("single", "f64", (47, 31, 29), KEEP), ("single", "f64", (39, 34, 48), STREAM), ("single", "f64", (46, 33, 47), STREAM),
+    ("single", "f32", (58, 61, 41), KEEP), ("single", "bf16", (84, 80, 43), KEEP), ("single", "f32", (51, 64, 50), STREAM),
+    ("immiscible", "f64", (24, 32, 23), KEEP), ("immiscible", "f64", (41, 30, 32), STREAM),
+    ("miscible", "f32", (34, 33, 33), KEEP), ("miscible", "f32", (40, 40, 40), STREAM),
+])
+def test_smallest_lattices(physics, storage, shape, want):
+    assert policies([[lattice(physics, storage, shape)]]) == [want]
