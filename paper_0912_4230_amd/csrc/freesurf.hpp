@@ -278,7 +278,9 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>:
     // lanes, as the step kernels of AllLanes do; the others' populations are
     // cleared below.  256^3 penetration step against a branch of the live
     // lanes: FP32 279 -> 270 us, FP16 split 246 -> 239, BF16 the same; 64^3 FP32
-    // 24.4 -> 23.4.
+    // 24.4 -> 23.4.  Their V is left as it comes: zeroed, as k_step's, for the
+    // sake of the drag's Newton iterations, the step took the same (256^3 270.0 /
+    // 271.1, 128^3 47.7 / 47.6, 64^3 23.3 / 23.6, 100 x 10 x 36 24.6 / 24.7 us).
     if (any_live) {
         Nbr b = neighbours(L, x, y, z, lw);
         b.bb = live ? b.bb : 0u;
@@ -859,7 +861,11 @@ __global__ __launch_bounds__(BLOCK) void k_fs_final(const BatchArgs a)
 // penetration FP64 21.7 / 19.2, 32^3 FP32 20.9 / 19.6, 38^3 BF16 20.7 / 20.6, 100
 // x 10 x 50 FP32 22.6 / 24.4: the converting cells of a large front keep one CU
 // longer than the launches take, so the line lies at 36 K cells, and at what
-// LDS holds for lattices one cell thick, whose front is a line.  (Scanning the
+// LDS holds for lattices one cell thick, whose front is a line.  Below it flat
+// boxes lose 3 to 5% (100 x 10 x 36 FP32 23.8 / 24.6, 90 x 8 x 50 BF16 24.9 / 26.1, but
+// 96 x 4 x 96 and 96 x 6 x 64 the same): the front is not known to the host.  Thin
+// lattices full of drops gain as well (140 of them on 200 x 280 FP64 51.5 / 51.1, 239 x
+// 239 FP32 47.6 / 47.0, 120 x 120 43.4 / 32.9).  (Scanning the
 // cells byte by byte, or working each off on the lane that found it, took 32
 // and 26 us for the drop, 32 and 42 for the 32^3 box.)
 constexpr int FS_SMALL_BLOCK = 1024;

@@ -254,7 +254,7 @@ using Launch = void (*)(const BatchArgs &, int blocks, hipStream_t);
 // 16-bit single-fluid and two-fluid steps are bound by issue and latency, not by
 // the number of streams in flight, and take the waves that fit (62 to 85 VGPRs):
 // channel 160^3 BF16 66.5 -> 61.3 us, 200^3 FP16 split 144 -> 139, 256^3 BF16 split
-// 296 -> 271 (BF16 the same, FP16 231 -> 234), two-fluid 128^3 BF16 77 -> 74,
+// 296 -> 271 (BF16 the same, FP16 231 -> 234; 200^3 116 -> 114, 128^3 27.5 -> 25.7), two-fluid 128^3 BF16 77 -> 74,
 // 256^3 545 -> 528, 157^3 FP16 split 166 -> 164.
 constexpr size_t STEP_LDS_RESERVE = 33 * 1024;
 
