@@ -42,6 +42,7 @@ struct CacheLattice {
     bool links, tensor;     // an obstacle mask; a full permeability tensor
     double cells, bytes;    // bytes: the populations (and split masses), both copies
     double medium;          // bytes of the other fields that a step reads
+    double bounced;         // share of the cells that have a link cut by the mask
 };
 
 // Cache policy of the populations in a step of these lattices (results are
@@ -97,8 +98,15 @@ struct CacheLattice {
 //     (36 MB) 1.9; whole lines in FP32: 17 to 25 MB -5, 35 MB 0, 39 MB (128 x 256 x 300)
 //     -1.3, 54 MB 2.5, 67 MB 3.1
 // So it gains again where a plane no longer fits in the L2s (32 MB together), and
-// up to two or three times the memory-side cache.  The obstacles' gain is that of
-// a tenth of the cells; BF16 and FP16 with a fiftieth range from -2 to 1.
+// up to two or three times the memory-side cache.  Between, with rows of whole lines,
+// it depends on how many cells have a bounced link.  Mean gain in percent over
+// planes of 12 to 36 MB (1,290 random boxes with 4^3 cubes of solid) at shares of
+// 0 / 0.02 / 0.06 / 0.11 / 0.18 / 0.28: deviations -2.8 / -2 / -0.7 / 1 / 1.9 / 4.7, FP32 -4 /
+// -3.6 / 0 / 2.7 / 5.5 / 10, its tensor step -5 / -4 / -2.5 / - / 2 / 6, FP64 -3.8 / -3.1 / -2.4 /
+// -0.9 / 0.6 / 3.8, its tensor step -5 / -6 / -6 / -3.5 / -1.7 / 1, split -2.9 / -2.8 / -2 / -0.9 /
+// 0 / 0; a mask taken for obstacles whatever it held lost up to 10 there (FP64 128^3
+// 6, BF16 160^3 3.6, FP32 tensor 10).  The single-fluid and two-fluid steps gain 1 to 4 from
+// the first obstacles on; with none they range from -4 (256^3 FP32) to 2.
 //
 // The free-surface step leaves the gas cells out; KEEP from 50 to 256 MB of
 // populations there, STREAM else (us, whole step, STREAM / KEEP: 48^3 FP32 17 MB
@@ -166,22 +174,40 @@ inline double keep_bytes(const CacheLattice *l, int n)
     return a.bytes <= tiny || (a.bytes >= a.low && a.bytes <= 256 * CACHE_MB && a.all <= a.end) ? a.all : 0.0;
 }
 
+// The same of a lattice with an obstacle mask, whatever its rows: do its bounced
+// links pay for plain loads?
+inline bool bounces_pay(const CacheLattice &c, double plane, double bytes)
+{
+    const bool f64 = c.storage == LBM_F64;
+    const double b = c.bounced;
+    if (c.physics != LBM_MISCIBLE) return b > 0.004;
+    if (split_storage(c.storage)) {
+        if (plane > 35 || (plane > 24 && (c.tensor || c.solutes > 1))) return true;
+        return (plane > 30 && b > 0.05) || (plane > 24 && b > 0.12);
+    }
+    if (paired_storage(c.physics, c.storage)) {
+        if (c.solutes > 1) return true;
+        return c.tensor ? plane > 30 || bytes <= 400 : plane > 45 || bytes <= 450 || b > 0.09;
+    }
+    if (c.solutes > 1) return plane > 42 || b > (f64 ? 0.05 : 0.03);
+    if (c.tensor) return plane > 30 || b > (f64 ? (bytes <= 500 ? 0.1 : 0.25) : (bytes <= 600 ? 0.015 : 0.12));
+    return plane > (f64 ? 60 : 42) || b > (f64 ? (bytes <= 600 ? 0.05 : 0.15) : (bytes <= 600 ? 0.015 : 0.08));
+}
+
 // Does a lattice beyond the memory-side cache step faster under REUSE than under
 // STREAM, in a launch of so many cells?
 inline bool reuse_pays(const CacheLattice &c, double cells)
 {
     const bool paired = paired_storage(c.physics, c.storage);
     const size_t word = storage_bytes(c.storage) * (paired ? 2 : 1);
-    const bool shared = c.nx * word % (paired ? 32 : 128) != 0 || c.links;
+    const bool shared = c.nx * word % (paired ? 32 : 128) != 0;
     const double plane = cells * double(word) / CACHE_MB, bytes = c.bytes / CACHE_MB;
+    if (c.links && bounces_pay(c, plane, bytes)) return true;
     if (!shared) return c.tensor && c.storage == LBM_F32 && plane > 42;
     if (c.physics != LBM_MISCIBLE) return true;
-    if (split_storage(c.storage)) return plane > (c.tensor || c.links || c.solutes > 1 ? 24 : 35);
-    if (paired) {
-        if (c.solutes > 1 || (c.links && !c.tensor)) return true;
-        return plane > (c.tensor && c.links ? 30 : 35) || bytes <= (c.tensor ? 400 : 600);
-    }
-    return !c.tensor || c.links || c.solutes > 1 || plane > 29 || bytes <= (c.storage == LBM_F64 ? 500 : 600);
+    if (split_storage(c.storage)) return plane > (c.tensor || c.solutes > 1 ? 24 : 35);
+    if (paired) return c.solutes > 1 || plane > 35 || bytes <= (c.tensor ? 400 : 600);
+    return !c.tensor || c.solutes > 1 || plane > 29 || bytes <= (c.storage == LBM_F64 ? 500 : 600);
 }
 
 inline bool launch_reuses(const CacheLattice *l, int n)

@@ -18,6 +18,8 @@
 
 namespace plbm {
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int NQ = 19;
 
 constexpr uint32_t bit(int q) { return 1u << q; }

@@ -454,7 +454,6 @@ __global__ PLBM_STEP_ATTR __attribute__((amdgpu_waves_per_eu(FsWaves<S, FT, ST>:
 //       the next step clears the marks of interface cells.
 constexpr int FS_CPT = 16;
 enum { FS_BORN = 1, FS_KEEP = 2, FS_TO_IF = 4, FS_RECV = 8 };
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct FsTile {
     const LatDev *L;

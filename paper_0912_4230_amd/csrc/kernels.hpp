@@ -1612,11 +1612,28 @@ struct InitArgs {
 template <class R>
 __device__ inline bool bad(R v) { return !isfinite(v); }
 
+// Adds to *count the cells of this wave (at c, with link word w) that have a link
+// cut by the obstacle mask.  Those next to a wall face are left out: the face cuts
+// links of theirs.
+__device__ inline void count_bounced(const LatDev *L, const int c[3], uint32_t w, int *count)
+{
+    const int n[3] = {L->nx, L->ny, L->nz};
+    bool cut = w != 0u && !(w & 1u);
+    for (int a = 0; a < 3; ++a) {
+        if (((L->wall_faces >> (2 * a)) & 1u) && c[a] == 1) cut = false;
+        if (((L->wall_faces >> (2 * a + 1)) & 1u) && c[a] == n[a] - 2) cut = false;
+    }
+    const uint64_t m = __builtin_amdgcn_ballot_w64(cut);
+    if ((threadIdx.x & 63) == 0 && m) atomicAdd(count, int(__popcll(m)));
+}
+
 // Link words of the obstacle mask: bit 0 = the cell is solid (wall face or
 // mask), bit q = the cell x - v_q is solid (periodic axes wrap).  Cells on
 // the face plane of a non-periodic axis are never fluid and get bit 0 only.
 // solid may be null (no obstacles: the words then encode the walls alone).
-__global__ __launch_bounds__(BLOCK) void k_links(const LatDev *L, const unsigned char *solid, uint32_t *links)
+// Every stride-th block adds its cells with a link cut by the mask to *count.
+__global__ __launch_bounds__(BLOCK) void k_links(const LatDev *L, const unsigned char *solid, uint32_t *links, int *count,
+                                                 int stride)
 {
     const uint32_t idx = blockIdx.x * BLOCK + threadIdx.x;
     if (idx >= uint32_t(L->ncell)) return;
@@ -1647,6 +1664,17 @@ __global__ __launch_bounds__(BLOCK) void k_links(const LatDev *L, const unsigned
         }
     }
     links[idx] = w;
+    if (blockIdx.x % uint32_t(stride) == 0) count_bounced(L, c, w, count);
+}
+
+// The same count of a mask that came with a loaded state.
+__global__ __launch_bounds__(BLOCK) void k_bounced(const LatDev *L, int *count, int stride)
+{
+    const uint32_t idx = blockIdx.x * uint32_t(stride) * BLOCK + threadIdx.x;
+    if (idx >= uint32_t(L->ncell)) return;
+    const uint32_t nxy = uint32_t(L->nx) * uint32_t(L->ny), r = idx % nxy;
+    const int c[3] = {int(r % uint32_t(L->nx)), int(r / uint32_t(L->nx)), int(idx / nxy)};
+    count_bounced(L, c, link_word(L, idx), count);
 }
 
 // Eigen-decomposition of a symmetric 3x3 matrix A = V diag(d) V^T by the

@@ -145,7 +145,7 @@ Layout layout(const lbm_desc *d)
     const size_t sb = storage_bytes(d->storage), rb = real_bytes(d->storage);
     size_t o = 0;
     L.lat = o;       o = align_up(o + sizeof(LatDev));
-    L.err = o;       o = align_up(o + sizeof(int));
+    L.err = o;       o = align_up(o + 2 * sizeof(int));
     L.diag = o;      o = align_up(o + 8 * sizeof(double));
     L.partials = o;  o = align_up(o + nb * NPART * sizeof(double));
     L.eps = o;       o = align_up(o + n * rb);
@@ -236,6 +236,7 @@ struct lbm_sim {
     int cur;            // copy holding the current state
     int ready;          // medium set
     int nblocks;
+    double bounced;     // share of the cells with a link cut by the obstacle mask
     int device;
     int in_scratch;     // workspace = this device's scratch array (lbm_create_static)
 };
@@ -476,6 +477,7 @@ CacheLattice cache_lattice(const lbm_sim *h)
     c.cells = h->host.ncell;
     c.bytes = double((d->physics == LBM_FREESURF ? h->lay.fs : h->lay.total) - h->lay.f0);
     const int planes = (h->host.uniform_eps ? 0 : 1) + (c.tensor ? 7 : (h->host.uniform_kinv ? 0 : 3)) + (h->host.rho1 ? 1 : 0);
+    c.bounced = h->bounced;
     c.medium = c.cells * double(planes * real_bytes(d->storage) + (c.links ? sizeof(uint32_t) : 0));
     return c;
 }
@@ -517,6 +519,18 @@ void launch_diag(lbm_sim *const *hs, int n, hipStream_t s)
     }
     if (c.n) hipLaunchKernelGGL(k_diag_part, dim3(c.total_blocks), dim3(BLOCK), 0, s, c);
     hipLaunchKernelGGL(k_diag_final, dim3(n), dim3(BLOCK), 0, s, a);
+}
+
+// The cells with a link cut by the mask are counted in every stride-th block of cells,
+// 64 to 128 of them in a large lattice (odd: of all rows in turn), behind the error
+// word.  In the kernel that makes the link words it costs the set-up nothing; over all
+// cells, in a launch of its own, 25 us (64^3) to 90 (256^3).
+int bounced_stride(const lbm_sim *h) { return h->nblocks / 64 | 1; }
+
+double bounced_share(const lbm_sim *h, int count)
+{
+    const int stride = bounced_stride(h), blocks = (h->nblocks + stride - 1) / stride;
+    return count / std::min(double(h->host.ncell), double(blocks) * BLOCK);
 }
 
 // One batched step for lattices hs[0..n) of the same physics, storage and
@@ -904,8 +918,8 @@ lbm_status lbm_set_medium(lbm_t h, const lbm_medium *m)
     for (int a = 0; a < 3; ++a) D.kinv_u[a] = m->kinv_uniform[a];
     lbm_status st;
     if ((st = dev_err(hipMemcpyAsync(h->dev, &D, sizeof(LatDev), hipMemcpyHostToDevice, h->stream)))) return st;
-    static const int zero = 0;
-    if ((st = dev_err(hipMemcpyAsync(D.err, &zero, sizeof(int), hipMemcpyHostToDevice, h->stream)))) return st;
+    static const int zero[2] = {0, 0};   // error, cells with bounced links
+    if ((st = dev_err(hipMemcpyAsync(D.err, zero, sizeof(zero), hipMemcpyHostToDevice, h->stream)))) return st;
     if (D.ms &&
         (st = dev_err(hipMemcpyAsync(const_cast<void *>(D.ms), &h->ms, sizeof(MsDev), hipMemcpyHostToDevice, h->stream))))
         return st;
@@ -923,7 +937,8 @@ lbm_status lbm_set_medium(lbm_t h, const lbm_medium *m)
         return st;
     if (D.links) {
         uint32_t *links = static_cast<uint32_t *>(const_cast<void *>(D.links));
-        hipLaunchKernelGGL(k_links, dim3(h->nblocks), dim3(BLOCK), 0, h->stream, (const LatDev *)h->dev, m->solid, links);
+        hipLaunchKernelGGL(k_links, dim3(h->nblocks), dim3(BLOCK), 0, h->stream, (const LatDev *)h->dev, m->solid, links,
+                           D.err + 1, bounced_stride(h));
     }
     if (D.full_tensor) {
         if (h->d.storage == LBM_F64)
@@ -942,12 +957,13 @@ lbm_status lbm_set_medium(lbm_t h, const lbm_medium *m)
     lbm_sim *one[1] = {h};
     launch_diag(one, 1, h->stream);
     if ((st = dev_err(hipGetLastError()))) return st;
-    int err = 0;
-    if ((st = dev_err(hipMemcpyAsync(&err, D.err, sizeof(int), hipMemcpyDeviceToHost, h->stream)))) return st;
+    int back[2] = {0, 0};
+    if ((st = dev_err(hipMemcpyAsync(back, D.err, sizeof(back), hipMemcpyDeviceToHost, h->stream)))) return st;
     if ((st = dev_err(hipStreamSynchronize(h->stream)))) return st;
     h->steps = 0;
     h->cur = 0;
-    if (err) return LBM_EINVAL;
+    h->bounced = bounced_share(h, back[1]);
+    if (back[0]) return LBM_EINVAL;
     h->ready = 1;
     return LBM_OK;
 }
@@ -1191,7 +1207,19 @@ lbm_status lbm_load_state(lbm_t h, const void *host_src, size_t bytes)
         if ((st = dev_err(hipMemcpyAsync(h->ws + sp[k].off, o, sp[k].len, hipMemcpyHostToDevice, h->stream)))) return st;
         o += sp[k].len;
     }
+    int bounced = 0;
+    if (h->host.links) {
+        // the mask came with the state, its count not with those saved before there was one
+        static const int zero = 0;
+        if ((st = dev_err(hipMemcpyAsync(h->host.err + 1, &zero, sizeof(int), hipMemcpyHostToDevice, h->stream)))) return st;
+        const int stride = bounced_stride(h);
+        hipLaunchKernelGGL(k_bounced, dim3((h->nblocks + stride - 1) / stride), dim3(BLOCK), 0, h->stream,
+                           (const LatDev *)h->dev, h->host.err + 1, stride);
+        if ((st = dev_err(hipGetLastError()))) return st;
+        if ((st = dev_err(hipMemcpyAsync(&bounced, h->host.err + 1, sizeof(int), hipMemcpyDeviceToHost, h->stream)))) return st;
+    }
     if ((st = dev_err(hipStreamSynchronize(h->stream)))) return st;
+    h->bounced = bounced_share(h, bounced);
     h->steps = H.steps;
     h->cur = int(H.cur);
     h->ready = 1;

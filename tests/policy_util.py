@@ -34,7 +34,7 @@ int policy(const CacheLattice *l, int n, const double *step) { return cache_poli
 class CacheLattice(C.Structure):
     _fields_ = [("physics", C.c_int), ("storage", C.c_int), ("nx", C.c_int), ("solutes", C.c_int),
                 ("links", C.c_bool), ("tensor", C.c_bool), ("cells", C.c_double), ("bytes", C.c_double),
-                ("medium", C.c_double)]
+                ("medium", C.c_double), ("bounced", C.c_double)]
 
 
 @functools.lru_cache(maxsize=None)
@@ -52,9 +52,10 @@ def _lib():
     return L
 
 
-def lattice(physics, storage, shape, links=False, tensor=False, species=1, uniform=None):
+def lattice(physics, storage, shape, links=False, tensor=False, species=1, uniform=None, bounced=None):
     """physics: single, miscible, immiscible or freesurf.  uniform: no medium planes (by default in the models
-    without one in their problems here).  The planes' padding is left out of the bytes."""
+    without one in their problems here).  bounced: the share of cells with a link cut by the mask (links), by
+    default as with a fifth of them solid.  The planes' padding is left out of the bytes."""
     k = {"single": B.LBM_SINGLE, "miscible": B.LBM_MISCIBLE, "immiscible": B.LBM_IMMISCIBLE, "freesurf": B.LBM_FREESURF}
     cells = float(np.prod(shape))
     copies = 1 if physics in ("single", "freesurf") else 1 + species
@@ -62,7 +63,8 @@ def lattice(physics, storage, shape, links=False, tensor=False, species=1, unifo
     uniform = physics in ("single", "immiscible") if uniform is None else uniform
     planes = (0 if uniform else (8 if tensor else 4)) + (physics == "immiscible")
     medium = cells * (planes * (8 if storage == "f64" else 4) + (4 if links else 0))
-    return CacheLattice(k[physics], B.STORAGE_NAMES[storage], shape[0], species, links, tensor, cells, cells * copies * each, medium)
+    return CacheLattice(k[physics], B.STORAGE_NAMES[storage], shape[0], species, links, tensor, cells, cells * copies * each, medium,
+                        (0.28 if bounced is None else bounced) if links else 0.0)
 
 
 def policies(groups):

@@ -86,6 +86,30 @@ def test_lines_of_the_miscible_step(storage, shape, options, want):
     assert policies([[lattice("miscible", storage, shape, **options)]]) == [want]
 
 
+@pytest.mark.parametrize("physics,storage,shape,line,options", [
+    ("miscible", "f32", (160, 160, 160), 0.08, {}), ("miscible", "f32", (192, 200, 120), 0.08, {}),
+    ("miscible", "f32", (128, 100, 100), 0.015, {}), ("miscible", "f32", (192, 128, 200), 0.12, {"tensor": True}),
+    ("miscible", "f64", (128, 128, 128), 0.15, {}), ("miscible", "f64", (96, 80, 90), 0.05, {}),
+    ("miscible", "f64", (128, 128, 128), 0.25, {"tensor": True}), ("miscible", "f64", (128, 128, 128), 0.05, {"species": 2}),
+    ("miscible", "f32", (160, 160, 160), 0.03, {"species": 2}), ("miscible", "bf16", (160, 160, 160), 0.09, {}),
+    ("miscible", "f16", (200, 200, 200), 0.09, {}), ("miscible", "f16", (212, 169, 122), 0.09, {}),
+    ("miscible", "bf16s", (200, 190, 180), 0.12, {}), ("miscible", "f16s", (200, 200, 200), 0.05, {}),
+    ("single", "f32", (256, 256, 256), 0.004, {}), ("immiscible", "f32", (128, 128, 128), 0.004, {}),
+])
+def test_obstacles_count_by_their_bounced_links(physics, storage, shape, line, options):
+    at = [policies([[lattice(physics, storage, shape, links=True, bounced=b, **options)]])[0]
+          for b in (0.0, 0.9 * line, 1.1 * line)]
+    assert at == [STREAM, STREAM, REUSE]
+
+
+@pytest.mark.parametrize("storage,shape,options", [
+    ("f32", (256, 256, 256), {}), ("f64", (256, 256, 120), {}), ("bf16", (256, 256, 256), {}), ("bf16", (128, 120, 130), {"species": 2}),
+    ("bf16", (128, 120, 130), {}), ("f16s", (256, 256, 256), {}), ("f16s", (256, 200, 140), {"species": 2}),
+    ("f32", (243, 251, 238), {}), ("f16", (151, 124, 112), {})])
+def test_plain_loads_pay_whatever_the_mask_holds(storage, shape, options):
+    assert policies([[lattice("miscible", storage, shape, links=True, bounced=0.0, **options)]]) == [REUSE]
+
+
 def test_planes_of_a_launch_add_up():
     a, b = lattice("miscible", "bf16", (187, 187, 187)), lattice("miscible", "bf16", (162, 162, 162))
     assert policies([[a]]) == policies([[b]]) == [STREAM] and policies([[a, b]]) == [REUSE]
